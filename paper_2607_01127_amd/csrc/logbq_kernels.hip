@@ -747,25 +747,41 @@ __global__ __launch_bounds__(512) void k_gemv(const uint16_t* __restrict__ x,
 
 // ------------------------------------------------------------------ GPTQ calibration
 //
-// Rows of W evolve independently given U, so the column loop runs one wavefront per row: lane
-// l holds columns i1 + l and i1 + 64 + l of the current block. Column i's value is read across
-// the wavefront (v_readlane), quantized to the fixed codebook by threshold counting (the same
-// decision as the encoders), and err = (w - q) / U_ii is subtracted, times U_ij, from the
-// block's later columns held by the lanes; the block's rows of U sit in LDS. After the block a
-// second kernel subtracts sum_i err_i U_ij from every later column (16 rows x 64 columns per
-// workgroup, the block's errors and U rows staged in LDS). Every operation is a separately
-// rounded float32 operation in a fixed order (no contraction), which fixes the result bits.
+// Rows of W evolve independently given U, and every element's updates form one ordered chain, so
+// the work may be blocked freely as long as each element meets its updates in column order.
+// Every operation is a separately rounded float32 operation in that order (no contraction),
+// which fixes the result bits.
+//
+// k_gptq_panel: 16 lanes share a row of the current block of 128 columns; lane r of them holds
+// columns 16 t + r (t = 0 .. 7) in registers. The block runs in eight slots of 16 columns. At every
+// step of a slot all 16 lanes quantize their own column and the step's lane broadcasts its error
+// inside the row (a DPP operand of the multiplications). The U rows sit in LDS. Bound by the
+// chain of one column's decision, division and update into the next (about 75 ns a step with one
+// wavefront per SIMD) and, from 8192 rows on, by VALU issue. One wavefront per row, which repeated
+// every decision in 64 lanes and loaded U one vector at a time, took 134 us per block of
+// 8192 rows; this takes 26 us (511 rows: 50 -> 14 us).
+// k_gptq_trail: subtracts sum_i err_i U_ij from every column after the block; 64 x 64 tiles, 4 x 4
+// outputs per thread, 32 columns of errors and U rows at a time through LDS. Two rounded
+// operations per product make the VALU its bound: at 8192 x 2048 it runs 43 T of them a second, 54 us
+// on average per block, where 16 x 64 tiles, reading five LDS words per four products, took
+// 117 us. The whole calibration, MI355X: 8192 x 2048 3.87 -> 1.21 ms, 2048 x 2048 1.50 -> 0.61 ms
+// (baseline quantizer 1.62 -> 0.68 ms), 511 x 1824 1.15 -> 0.51 ms.
 constexpr int kGptqBlock = 128;
+constexpr int kGptqRows = 16;    // rows per panel workgroup (4 wavefronts of 4 rows)
 
 struct GptqQuant {
   float cb[16];      // value of each code
   float th[15];      // LogbQuant: 7 magnitude thresholds on |w|; baseline: 15 on w
-  int uniform;       // 0: sign + magnitude (LogbQuant), 1: unsigned code (baseline)
+  int kind;          // kGptqLog, kGptqLogAny or kGptqUniform
 };
+constexpr int kGptqLog = 0;      // sign + magnitude, negative values mirror the positive ones
+constexpr int kGptqLogAny = 1;   // sign + magnitude, any 16 values
+constexpr int kGptqUniform = 2;  // unsigned code (baseline)
 
+template <int KIND>
 __device__ __forceinline__ uint32_t gptq_code(float w, const GptqQuant& qz) {
   uint32_t c = 0;
-  if (qz.uniform) {
+  if (KIND == kGptqUniform) {
 #pragma unroll
     for (int t = 0; t < 15; ++t) c += (w >= qz.th[t]) ? 1u : 0u;
   } else {
@@ -777,87 +793,257 @@ __device__ __forceinline__ uint32_t gptq_code(float w, const GptqQuant& qz) {
   return c;
 }
 
-__global__ __launch_bounds__(512) void k_gptq_panel(float* __restrict__ w, int n_rows, int k_cols,
+// The codebook in vector registers. The compiler would otherwise turn a choice between two kernel
+// arguments into a load from the chosen one's address, a memory round trip at every step (and a
+// selection takes at most one scalar operand).
+template <int KIND>
+__device__ __forceinline__ void gptq_hold(GptqQuant& qz) {
+#pragma unroll
+  for (int i = 0; i < (KIND == kGptqLog ? 8 : 16); ++i) asm("" : "+v"(qz.cb[i]));
+}
+
+// cb[the number of the N = 2^k - 1 ascending thresholds at or below v], by a tree of selections on
+// the comparisons' lane masks (all independent; the middle one decides last). The masks are all
+// formed before the first selection, each in its own register pair: compared and selected one by
+// one through VCC, every selection waits for its comparison.
+template <int N>
+__device__ __forceinline__ float gptq_pick(const uint64_t* ge, const float* cb) {
+  if constexpr (N == 0) {
+    return cb[0];
+  } else {
+    constexpr int H = N / 2;
+    const float lo = gptq_pick<H>(ge, cb), hi = gptq_pick<H>(ge + H + 1, cb + H + 1);
+    return __builtin_amdgcn_inverse_ballot_w64(ge[H]) ? hi : lo;
+  }
+}
+template <int N>
+__device__ __forceinline__ void gptq_masks(float v, const float* th, uint64_t (&ge)[N]) {
+#pragma unroll
+  for (int t = 0; t < N; ++t) ge[t] = __builtin_amdgcn_ballot_w64(v >= th[t]);
+  if constexpr (N == 7)
+    asm("" : "+s"(ge[0]), "+s"(ge[1]), "+s"(ge[2]), "+s"(ge[3]), "+s"(ge[4]), "+s"(ge[5]), "+s"(ge[6]));
+  else
+    asm("" : "+s"(ge[0]), "+s"(ge[1]), "+s"(ge[2]), "+s"(ge[3]), "+s"(ge[4]), "+s"(ge[5]),
+        "+s"(ge[6]), "+s"(ge[7]), "+s"(ge[8]), "+s"(ge[9]), "+s"(ge[10]), "+s"(ge[11]),
+        "+s"(ge[12]), "+s"(ge[13]), "+s"(ge[14]));
+}
+
+// cb[gptq_code(w)], except that a mirrored codebook (FAST) gives -0 instead of +0 for w = -0.
+template <int KIND, bool FAST>
+__device__ __forceinline__ float gptq_value(float w, const GptqQuant& qz) {
+  uint64_t ge[KIND == kGptqUniform ? 15 : 7];
+  const float a = KIND == kGptqUniform ? w : __builtin_fabsf(w);
+  gptq_masks(a, qz.th, ge);
+  if constexpr (KIND == kGptqUniform) return gptq_pick<15>(ge, qz.cb);
+  const float v = gptq_pick<7>(ge, qz.cb);
+  if (KIND == kGptqLog) return FAST ? __builtin_copysignf(v, w) : w < 0.0f ? -v : v;
+  float n = gptq_pick<7>(ge, qz.cb + 8);   // cb[8] is code 8, which is never produced
+  n = a >= qz.th[0] ? n : qz.cb[0];
+  return w < 0.0f ? n : v;
+}
+
+// a / d, correctly rounded, for moderate d > 0 and r = 1 / d correctly rounded: a * r and two
+// residual corrections with fused multiply-adds (Markstein's theorem: the first makes the quotient
+// faithful, the second rounds it correctly). Exact for a = +0 and 2^-60 <= |a| < 2^60.
+__device__ __forceinline__ float gptq_div(float a, float d, float r) {
+  const float q0 = a * r;
+  const float q1 = __builtin_fmaf(__builtin_fmaf(-q0, d, a), r, q0);
+  return __builtin_fmaf(__builtin_fmaf(-q1, d, a), r, q1);
+}
+
+// Lane L of every row of 16 lanes, in all of them (row_newbcast).
+template <int L>
+__device__ __forceinline__ float row_lane(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+      0, __builtin_bit_cast(int, v), 0x150 + L, 0xF, 0xF, true));
+}
+
+// One step of a slot: every lane's error of its own column (d: its U_ii and 1 / U_ii), lane L's
+// applied to the lanes after it and to the NS - 1 slots after this one (u: row 16 t + L of U at this
+// lane's column of each, 0 up to the diagonal). FAST lets the lanes up to L subtract that zero
+// times the error, which leaves every value but -0 as it is.
+template <int KIND, bool FAST, int NS, int L>
+__device__ __forceinline__ void gptq_step(float (&p)[8], float& a, float& e, int r,
+                                          const float (&u)[NS], float2 d, const GptqQuant& qz) {
+#pragma clang fp contract(off)
+  a = p[0] - gptq_value<KIND, FAST>(p[0], qz);
+  e = FAST ? gptq_div(a, d.x, d.y) : __fdiv_rn(a, d.x);
+  const float next = p[0] - row_lane<L>(e) * u[0];
+  p[0] = FAST || r > L ? next : p[0];
+#pragma unroll
+  for (int q = 1; q < NS; ++q) p[q] = p[q] - row_lane<L>(e) * u[q];
+}
+
+// The 16 steps of a slot. A lane's last update comes before its own step, so p[0] ends as every
+// column's value at its quantization and a and e, formed again from it at each later step, its
+// difference to the codebook and its error.
+template <int KIND, bool FAST, int NS>
+__device__ __forceinline__ void gptq_steps(float (&p)[8], float& a, float& e, int r,
+                                           const float* u, float2 d, const GptqQuant& qz) {
+  float uv[16][NS];
+#pragma unroll
+  for (int l = 0; l < 16; ++l)
+#pragma unroll
+    for (int q = 0; q < NS; ++q) uv[l][q] = u[l * kGptqBlock + 16 * q + r];
+#define LOGBQ_STEP(L) gptq_step<KIND, FAST, NS, L>(p, a, e, r, uv[L], d, qz);
+  LOGBQ_STEP(0) LOGBQ_STEP(1) LOGBQ_STEP(2) LOGBQ_STEP(3)
+  LOGBQ_STEP(4) LOGBQ_STEP(5) LOGBQ_STEP(6) LOGBQ_STEP(7)
+  LOGBQ_STEP(8) LOGBQ_STEP(9) LOGBQ_STEP(10) LOGBQ_STEP(11)
+  LOGBQ_STEP(12) LOGBQ_STEP(13) LOGBQ_STEP(14) LOGBQ_STEP(15)
+#undef LOGBQ_STEP
+}
+
+// Slot s: its steps are one dependent chain, so they run straight through on the forms that are
+// exact for ordinary values, with as many later slots as the block has left (rounded up to even).
+// If a value of the wavefront turns out not to be ordinary, the slot runs again from its start on
+// the general forms: a difference that is -0, tiny, huge or not finite, a value of -0, or an
+// extreme U_ii.
+template <int KIND>
+__device__ __forceinline__ float gptq_slot(float (&p)[8], int s, int r, const float* u, float2 d,
+                                           const GptqQuant& qz) {
+  float a, e, p0[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) p0[q] = p[q];
+  if (s < 2) gptq_steps<KIND, true, 8>(p, a, e, r, u, d, qz);
+  else if (s < 4) gptq_steps<KIND, true, 6>(p, a, e, r, u, d, qz);
+  else if (s < 6) gptq_steps<KIND, true, 4>(p, a, e, r, u, d, qz);
+  else gptq_steps<KIND, true, 2>(p, a, e, r, u, d, qz);
+  constexpr uint32_t kMinusZero = 0x80000000u;
+  const float mag = __builtin_fabsf(a);
+  const bool plain = (mag >= 8.673617379884035e-19f && mag < 1.152921504606847e18f) ||
+                     __builtin_bit_cast(uint32_t, a) == 0u;   // 2^-60, 2^60
+  if (__any(d.y == 0.0f || !plain || __builtin_bit_cast(uint32_t, p[0]) == kMinusZero)) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) p[q] = p0[q];
+    gptq_steps<KIND, false, 8>(p, a, e, r, u, d, qz);
+  }
+  return e;
+}
+
+template <int KIND>
+__global__ __launch_bounds__(256) void k_gptq_panel(float* __restrict__ w, int n_rows, int k_cols,
                                                     const float* __restrict__ u, int i1, int nb,
                                                     GptqQuant qz, float* __restrict__ err,
                                                     uint8_t* __restrict__ codes) {
 #pragma clang fp contract(off)
-  __shared__ float s_u[kGptqBlock * kGptqBlock];
-  for (int idx = threadIdx.x; idx < nb * nb; idx += 512) {
-    const int a = idx / nb, b = idx % nb;
-    s_u[a * kGptqBlock + b] = u[(int64_t)(i1 + a) * k_cols + i1 + b];
+  // U with zeros up to the diagonal. Slots past the block's end are computed with whatever follows
+  // a row (the general form reads up to 112 words) and never used.
+  __shared__ __attribute__((aligned(16))) float s_u[kGptqBlock * kGptqBlock + 112];
+  __shared__ float2 s_diag[kGptqBlock];   // U_ii and 1 / U_ii (0: U_ii is not moderate)
+  gptq_hold<KIND>(qz);
+  const int t = threadIdx.x;
+  const int r = t & 15;
+  const int row = blockIdx.x * kGptqRows + (t >> 4);
+  const bool live = row < n_rows;
+  float* wr = w + (int64_t)(live ? row : n_rows - 1) * k_cols + i1;
+  float p[8];   // columns 16 q + r; nb is a multiple of 32
+#pragma unroll
+  for (int q = 0; q < 8; ++q) p[q] = 16 * q < nb ? wr[16 * q + r] : 0.0f;
+  // U's rows: vector t + 256 v is column 4 (t % 32) of row t / 32 + 8 v. All requests are in flight
+  // together.
+  const int ub = 4 * (t & 31);
+  f32x4 uv[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int a = (t >> 5) + 8 * v;
+    uv[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (a < nb && ub < nb && ub + 3 > a)
+      uv[v] = *reinterpret_cast<const f32x4*>(u + (int64_t)(i1 + a) * k_cols + i1 + ub);
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int a = (t >> 5) + 8 * v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) uv[v][q] = ub + q > a ? uv[v][q] : 0.0f;
+    *reinterpret_cast<f32x4*>(s_u + a * kGptqBlock + ub) = uv[v];
+  }
+  if (t < nb) {
+    const float d = u[(int64_t)(i1 + t) * k_cols + i1 + t];
+    const bool moderate = d >= 9.094947017729282e-13f && d < 1.099511627776e12f;   // 2^-40, 2^40
+    s_diag[t] = make_float2(d, moderate ? __fdiv_rn(1.0f, d) : 0.0f);
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 8 + (threadIdx.x >> 6);
-  if (row >= n_rows) return;
-  float* wr = w + (int64_t)row * k_cols + i1;
-  float p0 = lane < nb ? wr[lane] : 0.0f;
-  float p1 = 64 + lane < nb ? wr[64 + lane] : 0.0f;
-  uint32_t c0 = 0, c1 = 0;
-  for (int i = 0; i < nb; ++i) {
-    const float wi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-        __builtin_bit_cast(int, i < 64 ? p0 : p1), i & 63));
-    const uint32_t c = gptq_code(wi, qz);
-    const float e = __fdiv_rn(wi - qz.cb[c], s_u[i * kGptqBlock + i]);
-    if (lane == (i & 63)) {
-      if (i < 64) c0 = c; else c1 = c;
+  for (int s = 0; 16 * s < nb; ++s) {
+    const float* us = s_u + 16 * s * (kGptqBlock + 1);   // row l of the slot at us + l * kGptqBlock
+    const float2 d = s_diag[16 * s + r];
+    const float e = gptq_slot<KIND>(p, s, r, us, d, qz);
+    const uint32_t c = gptq_code<KIND>(p[0], qz);
+    const uint32_t c1 = __builtin_amdgcn_update_dpp(0, (int)c, 0xB1, 0xF, 0xF, true);
+    if (live) {
+      wr[16 * s + r] = p[0];
+      err[(int64_t)row * kGptqBlock + 16 * s + r] = e;
+      if ((r & 1) == 0)
+        codes[(int64_t)row * (k_cols / 2) + (i1 + 16 * s + r) / 2] = (uint8_t)(c | (c1 << 4));
     }
-    if (lane == 0) err[(int64_t)row * kGptqBlock + i] = e;
-    const float* ui = s_u + i * kGptqBlock;
-    if (lane > i && lane < nb) p0 = p0 - e * ui[lane];
-    if (64 + lane > i && 64 + lane < nb) p1 = p1 - e * ui[64 + lane];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) p[q] = p[q + 1];
   }
-  if (lane < nb) wr[lane] = p0;
-  if (64 + lane < nb) wr[64 + lane] = p1;
-  // Byte b of the block holds columns 2b (low nibble) and 2b + 1.
-  const int src = (2 * lane) & 63;
-  const uint32_t lo0 = __builtin_amdgcn_ds_bpermute(src << 2, (int)c0);
-  const uint32_t hi0 = __builtin_amdgcn_ds_bpermute((src + 1) << 2, (int)c0);
-  const uint32_t lo1 = __builtin_amdgcn_ds_bpermute(src << 2, (int)c1);
-  const uint32_t hi1 = __builtin_amdgcn_ds_bpermute((src + 1) << 2, (int)c1);
-  const uint32_t byte = lane < 32 ? (lo0 | (hi0 << 4)) : (lo1 | (hi1 << 4));
-  if (2 * lane < nb) codes[(int64_t)row * (k_cols / 2) + i1 / 2 + lane] = (uint8_t)byte;
 }
 
+constexpr int kTrailTile = 64;   // rows and columns per workgroup
+constexpr int kTrailK = 32;      // errors per LDS stage (block widths are multiples of 32)
 __global__ __launch_bounds__(256) void k_gptq_trail(float* __restrict__ w, int n_rows, int k_cols,
                                                     const float* __restrict__ u, int i1, int nb,
                                                     const float* __restrict__ err) {
 #pragma clang fp contract(off)
-  __shared__ float s_e[16][kGptqBlock];
-  __shared__ __attribute__((aligned(16))) float s_u[kGptqBlock][64];
-  const int i2 = i1 + nb;
-  const int r0 = blockIdx.y * 16;
-  const int c0 = i2 + blockIdx.x * 64;
-  for (int idx = threadIdx.x; idx < 16 * kGptqBlock; idx += 256) {
-    const int r = idx / kGptqBlock, i = idx % kGptqBlock;
-    s_e[r][i] = (r0 + r < n_rows && i < nb) ? err[(int64_t)(r0 + r) * kGptqBlock + i] : 0.0f;
-  }
-  for (int idx = threadIdx.x; idx < kGptqBlock * 64; idx += 256) {
-    const int i = idx / 64, c = idx % 64;
-    s_u[i][c] = (i < nb && c0 + c < k_cols) ? u[(int64_t)(i1 + i) * k_cols + c0 + c] : 0.0f;
-  }
-  __syncthreads();
-  const int r = threadIdx.x >> 4;          // 16 rows
-  const int cq = (threadIdx.x & 15) * 4;   // 4 columns each
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int i = 0; i < nb; ++i) {
-    const float e = s_e[r][i];
-    const f32x4 uv = *reinterpret_cast<const f32x4*>(&s_u[i][cq]);
-    acc[0] = acc[0] + e * uv.x;
-    acc[1] = acc[1] + e * uv.y;
-    acc[2] = acc[2] + e * uv.z;
-    acc[3] = acc[3] + e * uv.w;
-  }
-  const int row = r0 + r;
-  if (row >= n_rows) return;
+  __shared__ __attribute__((aligned(16))) float s_e[2][kTrailK][kTrailTile];   // [i][row]
+  __shared__ __attribute__((aligned(16))) float s_u[2][kTrailK][kTrailTile];   // [i][column]
+  const int t = threadIdx.x;
+  const int c0 = i1 + nb + blockIdx.x * kTrailTile;
+  const int r0 = blockIdx.y * kTrailTile;
+  // Staging: a thread takes 8 errors (one row, 8 columns i) and two vectors of four columns of U.
+  // Rows past n_rows repeat the last one and columns past k_cols the last four (k_cols is a
+  // multiple of 32): computed, not stored.
+  const int er = r0 + (t & 63) < n_rows ? r0 + (t & 63) : n_rows - 1;
+  const float* ep = err + (int64_t)er * kGptqBlock + 8 * (t >> 6);
+  const int uc = c0 + 4 * (t & 15) < k_cols ? c0 + 4 * (t & 15) : k_cols - 4;
+  const float* up = u + (int64_t)(i1 + (t >> 4)) * k_cols + uc;
+  f32x4 ev[2], uv[2];
+  auto load = [&](int i) {
+    ev[0] = *reinterpret_cast<const f32x4*>(ep + i);
+    ev[1] = *reinterpret_cast<const f32x4*>(ep + i + 4);
+    uv[0] = *reinterpret_cast<const f32x4*>(up + (int64_t)i * k_cols);
+    uv[1] = *reinterpret_cast<const f32x4*>(up + (int64_t)(i + 16) * k_cols);
+  };
+  auto store = [&](int b) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int col = c0 + cq + q;
-    if (col < k_cols) {
-      float* p = w + (int64_t)row * k_cols + col;
-      *p = *p - acc[q];
+    for (int q = 0; q < 4; ++q) {
+      s_e[b][8 * (t >> 6) + q][t & 63] = ev[0][q];
+      s_e[b][8 * (t >> 6) + 4 + q][t & 63] = ev[1][q];
     }
+    *reinterpret_cast<f32x4*>(&s_u[b][t >> 4][4 * (t & 15)]) = uv[0];
+    *reinterpret_cast<f32x4*>(&s_u[b][16 + (t >> 4)][4 * (t & 15)]) = uv[1];
+  };
+  const int tr = 4 * (t >> 4), tc = 4 * (t & 15);
+  f32x4 acc[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) acc[a] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  load(0);
+  store(0);
+  __syncthreads();
+  int b = 0;
+  for (int i0 = 0; i0 < nb; i0 += kTrailK, b ^= 1) {
+    if (i0 + kTrailK < nb) load(i0 + kTrailK);
+#pragma unroll 8
+    for (int i = 0; i < kTrailK; ++i) {
+      const f32x4 e = *reinterpret_cast<const f32x4*>(&s_e[b][i][tr]);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&s_u[b][i][tc]);
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[a][q] = acc[a][q] + e[a] * v[q];
+    }
+    if (i0 + kTrailK < nb) store(b ^ 1);
+    __syncthreads();
+  }
+  if (c0 + tc >= k_cols) return;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int row = r0 + tr + a;
+    if (row >= n_rows) break;
+    f32x4* q = reinterpret_cast<f32x4*>(w + (int64_t)row * k_cols + c0 + tc);
+    const f32x4 v = *q;
+    *q = v - acc[a];
   }
 }
 
@@ -2870,12 +3056,16 @@ int32_t gptq_validate(int64_t n, int64_t k, const logbq_params* p, const logbq_u
     for (int i = 0; i < 16; ++i) qz.cb[i] = p->codebook[i];
     for (int i = 0; i < 7; ++i) qz.th[i] = p->thresholds[i];
     for (int i = 7; i < 15; ++i) qz.th[i] = INFINITY;
-    qz.uniform = 0;
+    // The kernels mirror the positive values when the codebook is sign-symmetric, as fitted ones
+    // are; any other takes both halves.
+    bool mirrored = qz.cb[0] == 0.0f && !std::signbit(qz.cb[0]);
+    for (int i = 1; i < 8; ++i) mirrored = mirrored && qz.cb[8 + i] == -qz.cb[i];
+    qz.kind = mirrored ? kGptqLog : kGptqLogAny;
   } else {
     if (uniform->bits != 4) return LOGBQ_ERR_UNSUPPORTED;
     for (int i = 0; i < 16; ++i) qz.cb[i] = uniform->codebook[i];
     for (int i = 0; i < 15; ++i) qz.th[i] = uniform->thresholds[i];
-    qz.uniform = 1;
+    qz.kind = kGptqUniform;
   }
   for (int i = 0; i < 16; ++i)
     if (!std::isfinite(qz.cb[i])) return LOGBQ_ERR_INVALID_ARG;
@@ -2893,12 +3083,19 @@ int32_t gptq_launch(float* w_dev, int N, int K, const float* u_dev, const GptqQu
                     float* err_dev, uint8_t* codes_dev, hipStream_t st) {
   for (int i1 = 0; i1 < K; i1 += kGptqBlock) {
     const int nb = K - i1 < kGptqBlock ? K - i1 : kGptqBlock;
-    hipLaunchKernelGGL(k_gptq_panel, dim3((unsigned)((N + 7) / 8)), dim3(512), 0, st, w_dev, N, K,
-                       u_dev, i1, nb, qz, err_dev, codes_dev);
+    const dim3 rows((unsigned)((N + kGptqRows - 1) / kGptqRows));
+#define LOGBQ_PANEL(KIND)                                                                      \
+  hipLaunchKernelGGL(k_gptq_panel<KIND>, rows, dim3(256), 0, st, w_dev, N, K, u_dev, i1, nb, qz, \
+                     err_dev, codes_dev)
+    if (qz.kind == kGptqLog) LOGBQ_PANEL(kGptqLog);
+    else if (qz.kind == kGptqLogAny) LOGBQ_PANEL(kGptqLogAny);
+    else LOGBQ_PANEL(kGptqUniform);
+#undef LOGBQ_PANEL
     if (launch_status() != LOGBQ_OK) return LOGBQ_ERR_HIP;
     if (i1 + nb < K) {
-      hipLaunchKernelGGL(k_gptq_trail, dim3((unsigned)((K - i1 - nb + 63) / 64), (unsigned)((N + 15) / 16)),
-                         dim3(256), 0, st, w_dev, N, K, u_dev, i1, nb, err_dev);
+      const dim3 tiles((unsigned)((K - i1 - nb + kTrailTile - 1) / kTrailTile),
+                       (unsigned)((N + kTrailTile - 1) / kTrailTile));
+      hipLaunchKernelGGL(k_gptq_trail, tiles, dim3(256), 0, st, w_dev, N, K, u_dev, i1, nb, err_dev);
       if (launch_status() != LOGBQ_OK) return LOGBQ_ERR_HIP;
     }
   }

@@ -27,3 +27,68 @@ def test_dequantize_tiles(bits, n, k):
     got = out.cpu().numpy()
     assert np.array_equal(got[:n * k].reshape(n, k), book[c])
     assert np.all(got[n * k:] == 7.0)
+
+
+def _gptq_case(n, k, seed):
+    rng = np.random.default_rng(seed)
+    w = (0.02 * rng.standard_t(4, size=(n, k))).astype(np.float32)
+    u = np.triu(0.1 * rng.standard_normal((k, k)), 1).astype(np.float32)
+    u[np.arange(k), np.arange(k)] = np.exp(rng.normal(0, 0.5, k)).astype(np.float32)
+    return rng, w, u
+
+
+def _special_rows(rng, w, u):
+    """Values whose errors the short division does not cover: zeros of both signs, subnormal, tiny
+    and huge weights, infinities and NaN, and extreme diagonal entries of U."""
+    n, k = w.shape
+    w[:, 5] = 0.0
+    w[:, 6] = -0.0
+    w[0, ::3] = 0.0
+    w[1 % n, ::3] = -0.0
+    w[2 % n] *= np.float32(1e-36)
+    w[3 % n] *= np.float32(1e30)
+    w[4 % n, 17 % k] = np.inf
+    w[5 % n, k - 1] = -np.inf
+    w[6 % n, 3] = np.nan
+    u[7, 7] = np.float32(1e-30)
+    if k > 200:
+        u[150, 150] = np.float32(1e25)
+        u[40, 45:] = 0.0
+        u[41, 50:] = -0.0
+
+
+@pytest.mark.parametrize("n,k", [(1, 32), (15, 64), (17, 96), (16, 128), (65, 224), (33, 256)])
+@pytest.mark.parametrize("book", ["mirrored", "any", "uniform"])
+@pytest.mark.parametrize("special", [False, True])
+def test_gptq_edges(n, k, book, special):
+    """Ragged rows and last blocks, and values outside the short division's range, for each kind of
+    codebook, bit for bit against the CPU oracle's float32 loop."""
+    from oracle import gptq_oracle as G
+    print(f"gptq edges n={n} k={k} {book} special={special}", flush=True)
+    rng, w, u = _gptq_case(n, k, [7, n, k])
+    fit_on = (0.02 * rng.standard_t(4, size=4096)).astype(np.float32)
+    p = L.fit_uniform(fit_on) if book == "uniform" else L.fit(fit_on)
+    if book == "any":
+        for i in range(1, 8):
+            p.codebook[8 + i] *= 1.125
+        p.codebook[0] = 0.001
+    if special:
+        _special_rows(rng, w, u)
+    levels, th = p.codebook_array(), np.ctypeslib.as_array(p.thresholds).copy()
+
+    def quantize(col):
+        if book == "uniform":
+            c = np.sum(col[:, None] >= th[None, :15], axis=1)
+        else:
+            c = np.sum(np.abs(col)[:, None] >= th[None, :7], axis=1)
+            c = np.where((col < 0) & (c > 0), c + 8, c)
+        return c.astype(np.uint8), levels[c]
+
+    with np.errstate(all="ignore"):
+        codes_ref, w_ref = G.gptq(w, u, quantize)
+    wd = torch.from_numpy(w.copy()).to(DEV)
+    codes = L.gptq(wd, torch.from_numpy(u).to(DEV), p)
+    got, wg = codes.cpu().numpy(), wd.cpu().numpy()
+    assert np.array_equal(got, codes_ref[:, 0::2] | (codes_ref[:, 1::2] << 4))
+    same = (wg.view(np.uint32) == w_ref.view(np.uint32)) | (np.isnan(wg) & np.isnan(w_ref))
+    assert same.all(), f"{np.count_nonzero(~same)} of {same.size} weights differ"
