@@ -22,6 +22,8 @@
 //   k_mfma_kq  the same product for m > 96: each wavefront takes 64 weight rows and one K
 //              quarter of every step for all 128 batch rows of the workgroup; the quarters'
 //              tiles are summed through LDS at the end (k_mfma_kq8: the same on 8-bit codes).
+//   k_mfma_pf  the same product for m > 256 (prefill): 256 weight rows x 64 to 256 batch rows per
+//              workgroup, dequantization and staging issued between the MFMAs of the slice before.
 //   k_encode8, k_dequant8, k_gemv<8, ...>, k_mfma2<8, ...>  the same on 8-bit codes.
 //   k_encode_uniform  codes of the asymmetric linear baseline (Sec. 2), for comparisons.
 //   k_gptq_panel, k_gptq_trail  GPTQ calibration with a fixed codebook (one wavefront per row
@@ -1693,6 +1695,316 @@ __global__ __launch_bounds__(512) void k_mfma_kq8(const uint8_t* __restrict__ co
   }
 }
 
+// ------------------------------------------------------------------ MFMA GEMM, prefill
+//
+// Hundreds to thousands of batch rows: bound by the matrix cores, so everything else has to
+// issue beside them. A workgroup of 8 wavefronts owns 256 weight rows x 64 BT batch rows and walks
+// K in slices of 16; wavefront (wb, wn) = (wave / 4, wave % 4) takes 32 BT batch rows x 64 weight
+// rows: 2 BT MFMAs of 32x32x16 per slice, and between them the dequantization of the next slice's
+// two weight fragments, the LDS reads of its activation fragments and a quarter of the staging of
+// a later tile.
+//
+// Steps are 64 k: lane (j, g) = (lane % 32, lane / 32) holds k = step + 32 g + 0..31 of its weight
+// rows, and slice c contracts k = step + 32 g + 8 c + 0..7.
+//
+// Why 32x32x16: beside it two wavefronts issue 3 VALU instructions per 16 cycles of MFMA at no
+// cost, beside 16x16x32 only 2 (measured). Why a table and not dequantization in registers: 8
+// instead of 14 VALU instructions per eight weights, with LDS reads to spare, and any codebook
+// (14336 x 4096 at m = 1024, registers against table: 142 / 133 us with two batch tiles, 108 / 111
+// with four). Why one barrier per step and not halves that alternate: a wavefront alone on its SIMD
+// issues VALU every 8 cycles only (half a slice apart: 87 us against 72 on 4096 x 4096 at m = 512).
+// 14336 x 4096 at m = 2048: 316 -> 223 us (1.08 PFLOP/s, where a plain float16 matrix product of the
+// library takes 192 us); what bounds it is the clock under the matrix load: the same grid with a
+// codebook of smaller mantissas takes 178 us.
+//
+// LDS holds three activation tiles [64 BT rows][64 k] and the codes of two steps, both without
+// padding: 16-byte unit u of activation row r is stored at u ^ (r / 2) % 8, and the codes' units
+// are exchanged likewise, so that the 16 lanes a 128-bit read serves together (0-3, 12-15 and
+// 20-27, or 4-11, 16-19 and 28-31, and the same from 32 on) cover all 64 banks. The one barrier
+// of a step, before slice 2, lies between the writes of tile s + 1 (slices 2 and 3 of step s - 1,
+// 0 and 1 of step s) and its first reads (slice 3 of step s), and between the last reads of tile
+// s - 2 (slice 2 of step s - 2), whose slot it takes, and its writes.
+//
+// Results do not depend on the launch shape: every output is one sum over K in ascending
+// slices.
+//
+// K may come in two parts (workgroups of gridDim.y = 2, y zeroed beforehand, one atomic add each):
+// every output receives exactly two adds onto zero, which round the same in either order.
+//
+// Codes are looked up in an LDS table of float16 images (8 bits) or pairs of them (4 bits), 256
+// words with one copy per lane (64 KiB) or, where the tiles leave less room, one per lane of a
+// half wavefront (32 KiB), which costs one shift more per lookup.
+template <int BITS, int CP>
+__device__ __forceinline__ void pf_fill(uint32_t* s_lut, const typename LutOf<BITS>::type& lut) {
+  if constexpr (CP == 64) {
+    fill_lut<BITS, 512>(s_lut, lut);
+  } else {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      u32x4 v;
+      if constexpr (BITS == 4) {
+        // Vector t + 512 i holds the pair of nibbles (t / 8) % 16 and t / 128 + 4 i.
+        v = lut16_entry(lut, ((uint32_t)t >> 3) & 15u) |
+            (lut16_entry(lut, ((uint32_t)t >> 7) + 4u * i) << 16);
+      } else {
+        // Vector t + 512 i holds entry 8 w + lane / 8 + 64 i: half (lane / 8) % 2 of word
+        // 4 w + 32 i + lane / 16, read with uniform loads.
+        const int lane = t & 63;
+        const int h = 4 * __builtin_amdgcn_readfirstlane(t >> 6) + 32 * i;
+        const uint32_t a = lane & 16 ? lut.h[h + 1] : lut.h[h];
+        const uint32_t c = lane & 16 ? lut.h[h + 3] : lut.h[h + 2];
+        const uint32_t word = lane & 32 ? c : a;
+        v = lane & 8 ? word >> 16 : word & 0xFFFFu;
+      }
+      *reinterpret_cast<u32x4*>(s_lut + 4 * (t + 512 * i)) = v;
+    }
+  }
+}
+
+// LDS address of the table word for byte i of code dword d; off = (lane % CP) * (256 / CP).
+template <int CP>
+__device__ __forceinline__ const char* pf_word(const uint32_t* s_lut, uint32_t d, uint32_t off,
+                                               int i) {
+  const uint32_t a = __builtin_amdgcn_perm(d, off, 0x0C0C0000u | ((uint32_t)(4 + i) << 8));
+  return reinterpret_cast<const char*>(s_lut) + (CP == 64 ? a : a >> 1);
+}
+
+template <int BITS, int BT>
+__global__ __launch_bounds__(512) void k_mfma_pf(const uint8_t* __restrict__ codes,
+                                                 const uint16_t* __restrict__ x,
+                                                 float* __restrict__ y, int n_rows, int k_cols,
+                                                 int m_rows, int m_blocks, float scale,
+                                                 typename LutOf<BITS>::type lut) {
+  constexpr int STEP = 64;
+  constexpr int ROWS = 64 * BT;                    // batch rows per workgroup
+  constexpr int CP = BT <= (BITS == 4 ? 3 : 2) ? 64 : 32;   // table copies
+  constexpr int kTab = CP * 1024;
+  constexpr int kSlot = ROWS * STEP * 2;
+  constexpr int CB = BITS / 4;                     // code vectors per thread and step
+  constexpr int kCodes = CB * 512 * 16;
+  constexpr int kX = kTab + 2 * kCodes;
+  __shared__ __attribute__((aligned(16))) uint8_t s_mem[kX + 3 * kSlot];
+  uint32_t* s_lut = reinterpret_cast<uint32_t*>(s_mem);
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wb = wave >> 2, wn = wave & 3;
+  const int j = lane & 31;
+  const int g = lane >> 5;
+  const uint32_t laneoff = (uint32_t)(lane % CP) * (256 / CP);
+
+  // Workgroups go round-robin to the 8 XCDs; each XCD takes a contiguous run of tiles, batch
+  // blocks fastest, so the workgroups that share an L2 share codes and activations.
+  const int id = blockIdx.x, total = gridDim.x;
+  const int xcd = id & 7, per = total >> 3, rest = total & 7;
+  const int tile = xcd * per + (xcd < rest ? xcd : rest) + (id >> 3);
+  const int mb = (tile % m_blocks) * ROWS;
+  const int nb = (tile / m_blocks) * 256;
+
+  // Steps [s0, s_end) of the workgroup's K part.
+  const int steps_all = (k_cols + STEP - 1) / STEP;
+  const int part = (steps_all + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int s0 = (int)blockIdx.y * part;
+  const int s_end = s0 + part < steps_all ? s0 + part : steps_all;
+  const int row_bytes = k_cols * BITS / 8;
+  const int band_rows = n_rows - nb < 256 ? n_rows - nb : 256;
+  const int x_rows = m_rows - mb < ROWS ? m_rows - mb : ROWS;
+  // Descriptors over the workgroup's rows: rows past the end read as zeros. The row part of an
+  // offset is a lane's own and range-checked, the step is a scalar offset, and lanes past the end
+  // of a row take an offset past the end of the descriptor.
+  const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(codes + (int64_t)nb * row_bytes), (short)0, band_rows * row_bytes,
+      kBufferRsrcWord3);
+  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(x + (int64_t)mb * k_cols), (short)0, x_rows * k_cols * 2, kBufferRsrcWord3);
+  constexpr int kPastEnd = (int)0x80000000u;
+
+  // Activations: BT vectors per thread and step, unit xu of rows xr0 + 64 i.
+  const int xu = t & 7, xr0 = t >> 3;
+  const int x_off = (xr0 * k_cols + xu * 8) * 2;
+  const int x_lds = xr0 * (STEP * 2) + ((xu ^ ((xr0 >> 1) & 7)) << 4);
+  u32x4 xr[BT];
+  auto load_x = [&](int step, int i) {
+    const bool in = xu * 8 < k_cols - step * STEP;
+    xr[i] = __builtin_amdgcn_raw_buffer_load_b128(
+        xrs, in ? x_off + i * (64 * k_cols * 2) : kPastEnd, step * (STEP * 2), 0);
+  };
+  auto store_x = [&](int slot, int i) {
+    *reinterpret_cast<u32x4*>(s_mem + kX + slot + x_lds + i * (64 * STEP * 2)) =
+        xr[i];
+  };
+  const int a_row = (wb * 32 * BT + j) * (STEP * 2);
+  const int a_unit = (4 * g) ^ ((j >> 1) & 7);
+  half8v a[2][BT];
+  auto read_a = [&](int slot, int c, int bt) {
+    a[c & 1][bt] = *reinterpret_cast<const half8v*>(s_mem + kX + slot + a_row +
+                                                    ((a_unit ^ c) << 4) + bt * (32 * STEP * 2));
+  };
+
+  // Codes of a step: 32 or 64 bytes of each of the 256 rows, CB vectors of 16 bytes per thread.
+  constexpr int VR = 2 * CB;                       // vectors per row
+  const int c_off = (t / VR) * row_bytes + 16 * (t % VR);
+  const int c_lds = (t ^ ((t >> 4) & (VR - 1))) * 16;
+  u32x4 cr[CB];
+  auto load_codes = [&](int step) {
+    const bool in = 16 * (t % VR) < row_bytes - step * (32 * CB);
+#pragma unroll
+    for (int i = 0; i < CB; ++i)
+      cr[i] = __builtin_amdgcn_raw_buffer_load_b128(
+          crs, in ? c_off + i * (512 / VR) * row_bytes : kPastEnd, step * (32 * CB), 0);
+  };
+  auto store_codes = [&](int slot) {
+#pragma unroll
+    for (int i = 0; i < CB; ++i)
+      *reinterpret_cast<u32x4*>(s_mem + kTab + slot + i * 8192 + c_lds) = cr[i];
+  };
+  // This lane's codes of a step: 4 CB dwords of row 64 wn + 32 rt + j.
+  const int q_swz = CB == 1 ? (j >> 3) & 1 : (j >> 2) & 3;
+  uint32_t q[2][4 * CB];
+  auto read_codes = [&](int slot) {
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int i = 0; i < CB; ++i) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(
+            s_mem + kTab + slot + (64 * wn + 32 * rt + j) * (32 * CB) +
+            (((CB * g + i) ^ q_swz) << 4));
+        q[rt][4 * i] = v.x; q[rt][4 * i + 1] = v.y;
+        q[rt][4 * i + 2] = v.z; q[rt][4 * i + 3] = v.w;
+      }
+  };
+  u32x4 b[2][2];
+  auto dequant = [&](int c, int rt) {
+    u32x4 bw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (BITS == 4) {
+        bw[i] = *reinterpret_cast<const uint32_t*>(pf_word<CP>(s_lut, q[rt][c], laneoff, i));
+      } else {
+        const uint32_t d = q[rt][2 * c + (i >> 1)];
+        const uint32_t lo = *reinterpret_cast<const uint16_t*>(
+            pf_word<CP>(s_lut, d, laneoff, 2 * (i & 1)));
+        const uint32_t hi = *reinterpret_cast<const uint16_t*>(
+            pf_word<CP>(s_lut, d, laneoff, 2 * (i & 1) + 1));
+        bw[i] = lo | (hi << 16);
+      }
+    }
+    b[c & 1][rt] = bw;
+  };
+
+  float16v acc[BT][2];
+#pragma unroll
+  for (int bt = 0; bt < BT; ++bt)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) acc[bt][rt] = 0.0f;
+
+  // Vectors of activations and codes are loaded a step before they are written to LDS.
+  load_codes(s0);
+#pragma unroll
+  for (int i = 0; i < BT; ++i) load_x(s0, i);
+  pf_fill<BITS, CP>(s_lut, lut);
+  store_codes(0);
+  load_codes(s0 + 1);
+#pragma unroll
+  for (int i = 0; i < BT; ++i) {
+    store_x(0, i);
+    load_x(s0 + 1, i);
+  }
+#pragma unroll
+  for (int i = 0; i < 2 && i < BT; ++i) {
+    store_x(kSlot, i);
+    load_x(s0 + 2, i);
+  }
+  __syncthreads();
+  read_codes(0);
+#pragma unroll
+  for (int bt = 0; bt < BT; ++bt) read_a(0, 0, bt);
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) dequant(0, rt);
+
+  int cur = 0, nxt = kSlot, nn = 2 * kSlot;        // slots of tiles s, s + 1, s + 2
+  int cnext = kCodes;                              // slot of the codes of step s + 1
+  for (int step = s0; step < s_end; ++step) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (c == 2) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // The empty asm statements keep arithmetic in its slice: without them the compiler places
+      // it anywhere in the loop body.
+      const int cn = (c + 1) & 3;                  // next slice
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int i = 0; i < CB; ++i) asm volatile("" : "+v"(q[rt][CB * cn + i]));
+#pragma unroll
+      for (int bt = 0; bt < BT; ++bt) read_a(c == 3 ? nxt : cur, cn, bt);
+      if (c == 0) {
+#pragma unroll
+        for (int i = 0; i < CB; ++i) asm volatile("" : "+v"(cr[i]));
+        store_codes(cnext);
+        load_codes(step + 2);
+      }
+      const int xi = (c + 2) & 3;                  // vector staged in this slice
+      if (xi < BT) {
+        asm volatile("" : "+v"(xr[xi % BT]));
+        store_x(c < 2 ? nxt : nn, xi % BT);
+        load_x(c < 2 ? step + 2 : step + 3, xi % BT);
+      }
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) dequant(cn, rt);
+#pragma unroll
+      for (int bt = 0; bt < BT; ++bt)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+          acc[bt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+              a[c & 1][bt], __builtin_bit_cast(half8v, b[c & 1][rt]), acc[bt][rt], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 2 * BT; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);     // VALU
+      }
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) asm volatile("" : "+v"(b[cn & 1][rt]));
+      if (c == 2) read_codes(cnext);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int freed = cur;
+    cur = nxt;
+    nxt = nn;
+    nn = freed;
+    cnext = kCodes - cnext;
+  }
+
+  // Stores past the last row or weight go past the end of the descriptor and are dropped.
+  const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(y + (int64_t)mb * n_rows), (short)0, x_rows * n_rows * 4, kBufferRsrcWord3);
+#pragma unroll
+  for (int bt = 0; bt < BT; ++bt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = (wb * BT + bt) * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        const int row = nb + 64 * wn + 32 * rt + j;
+        const float v = acc[bt][rt][r] * scale;
+        if (gridDim.y > 1) {
+          if (m < x_rows && row < n_rows)
+            unsafeAtomicAdd(&y[(int64_t)(mb + m) * n_rows + row], v);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), yrs,
+                                                row < n_rows ? (m * n_rows + row) * 4 : kPastEnd,
+                                                0, 0);
+        }
+      }
+    }
+}
+
 // ------------------------------------------------------------------ split-K MFMA, m <= 16
 //
 // For T batch tiles of 16 rows (T = 1 for m <= 16, T = 2 for m <= 32) and K = 32 W ND KS (W
@@ -2468,6 +2780,7 @@ struct StepCfg {
   bool narrow;
   int mt16;
   int ks;
+  double cost;     // us by the model, negative where no shape fits
 };
 // The shape is the cheapest, by a cost model, of every shape whose grid fits on the chip at
 // once (at most one workgroup per CU): 64 or 128 rows, t = t0, t0 / 2, ... 1 batch tiles
@@ -2495,7 +2808,7 @@ StepCfg step_config(int M, int64_t N, int K, int bits, bool symmetric) {
   const int cap = reg ? 8 : 4;
   int t0 = (M + 15) / 16;
   if (t0 > cap) t0 = cap;
-  StepCfg best{narrow_fits(M, N, cap), t0, 1};
+  StepCfg best{narrow_fits(M, N, cap), t0, 1, -1.0};
   const StepCosts& cc = reg ? kCostsRegister : bits == 4 ? kCostsTable4 : kCostsTable8;
   const int64_t nsteps = ((int64_t)K + kM2Step - 1) / kM2Step;
   double best_cost = -1.0;
@@ -2514,7 +2827,7 @@ StepCfg step_config(int M, int64_t N, int K, int bits, bool symmetric) {
                             (ks == 2 ? cc.two_parts : 0.0);
         if (best_cost < 0.0 || cost < best_cost) {
           best_cost = cost;
-          best = {rows == 64, mt, ks};
+          best = {rows == 64, mt, ks, cost};
         }
       }
       if (mt == 1) break;
@@ -2658,6 +2971,73 @@ int32_t launch_kq(const uint16_t* x, int M, int K, const LinearJob& j, hipStream
   dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
   hipLaunchKernelGGL(k_mfma_kq, grid, dim3(512), 0, st, j.codes, x, j.y, N, K, M, tb, scale);
   return launch_status();
+}
+
+// Launch shape of the prefill kernel: 64 bt batch rows per workgroup and K in ks parts.
+struct PfCfg {
+  int bt, ks;
+  double cost;     // us by the model
+};
+// The cheapest by a cost model fitted to MI355X measurements (29 shapes, n = 512 .. 28672,
+// k = 512 .. 14336, m = 300 .. 2048, within 10 % of nearly all): every round of up to 256
+// workgroups costs 7 us and, per step of 64 k, step[bt - 1] us; the whole grid's matrix work slows
+// the clock by a further full_bt * bt us per step and full chip. Two K parts add the zeroing
+// launch and two atomic adds per output.
+PfCfg pf_config(int M, int64_t N, int K, int bits) {
+  static constexpr double step4[4] = {0.59, 0.69, 0.89, 1.13};
+  static constexpr double step8[4] = {1.03, 1.155, 1.516, 1.666};
+  const double full_bt = bits == 4 ? 0.115 : 0.08;
+  const int64_t steps = ((int64_t)K + 63) / 64;
+  PfCfg best{0, 0, -1.0};
+  for (int ks = 1; ks <= (steps >= 2 ? 2 : 1); ++ks)
+    for (int bt = 1; bt <= 4; ++bt) {
+      const int64_t wgs = ((M + 64 * (int64_t)bt - 1) / (64 * bt)) * ((N + 255) / 256) * ks;
+      const double rounds = (double)((wgs + 255) / 256);
+      const double per_step = (bits == 4 ? step4 : step8)[bt - 1] * rounds +
+                              full_bt * bt * (double)wgs / 256.0;
+      const double cost = 7.0 * rounds + (double)((steps + ks - 1) / ks) * per_step +
+                          (ks == 2 ? 3.0 + 8.5e-6 * (double)M * (double)N : 0.0);
+      if (best.cost < 0.0 || cost < best.cost) best = {bt, ks, cost};
+    }
+  return best;
+}
+
+// The prefill kernel takes more than 256 batch rows unless the stepped kernel has a launch shape
+// that fits on the chip at once and its model's time, plus 5 us of launch and edges that the model
+// leaves out, is the shorter: narrow layers, whose 256-row tiles would leave most CUs idle
+// (1024 x 4096 at m = 300: 18.0 us against 27.1; 4096 x 4096 at m = 512: 34.6 against 41.6).
+// Elsewhere it replaces the K-quartered and the stepped kernels (4-bit 14336 x 4096 at m = 2048:
+// 316 -> 223 us, 8192 x 2048 at m = 600: 54 -> 34; another codebook 14336 x 4096 at m = 2048:
+// 410 -> 178; 8-bit 8199 x 3072 at m = 777: 173 -> 72, 14336 x 4096 at m = 2048: 698 -> 275).
+// k < 2^22 and n < 2^21 keep the descriptors over 256 rows of codes, of activations and of y
+// below 2^31 bytes, m n < 2^36 the one-dimensional grid below 2^32 threads.
+bool pf_shape(int M, int64_t N, int K, int bits) {
+  if (M <= 256 || K >= (1 << 22) || N >= (1 << 21) || M * N >= ((int64_t)1 << 36)) return false;
+  const double stepped = step_config(M, N, K, bits, true).cost;
+  return stepped < 0.0 || pf_config(M, N, K, bits).cost < stepped + 5.0;
+}
+
+template <int BITS>
+int32_t launch_pf(const uint16_t* x, int M, int K, const LinearJob& j, hipStream_t st,
+                  int cus) {
+  const int N = (int)j.n;
+  typename LutOf<BITS>::type lut;
+  float scale;
+  make_lut<BITS>(j.codebook, &lut, &scale);
+  const PfCfg cfg = pf_config(M, N, K, BITS);
+  const int bt = cfg.bt;
+  const int m_blocks = (M + 64 * bt - 1) / (64 * bt);
+  const int64_t total = (int64_t)m_blocks * ((N + 255) / 256);
+  if (cfg.ks > 1) fill_zero(j.y, (int64_t)M * N, cus, st);
+#define LOGBQ_PF(BT)                                                                           \
+  if (bt == BT) {                                                                              \
+    hipLaunchKernelGGL((k_mfma_pf<BITS, BT>), dim3((unsigned)total, cfg.ks), dim3(512), 0, st, \
+                       j.codes, x, j.y, N, K, M, m_blocks, scale, lut);                        \
+    return launch_status();                                                                    \
+  }
+  LOGBQ_PF(1) LOGBQ_PF(2) LOGBQ_PF(3) LOGBQ_PF(4)
+#undef LOGBQ_PF
+  return LOGBQ_ERR_UNSUPPORTED;
 }
 
 // Split-K MFMA path: 4-bit codes, 2 <= m <= 32 at K in {1024, 2048, 4096, 8192}, and
@@ -2845,6 +3225,7 @@ int choose_path(int M, int K, int64_t N) {
   if (M <= 8 && gemv_config<BITS>(M, K, &wk, &cpl) &&
       !(M >= (BITS == 8 ? 5 : 3) && (int64_t)M * N > 65536))
     return LOGBQ_PATH_GEMV;
+  if (pf_shape(M, N, K, BITS)) return LOGBQ_PATH_MFMA_PF;
   if (BITS == 4 && kq_shape(M, N, K) && !narrow_fits(M, N)) return LOGBQ_PATH_MFMA_KQ;
   if (BITS == 8 && kq8_shape(M, N, K)) return LOGBQ_PATH_MFMA_KQ;
   return LOGBQ_PATH_MFMA;
@@ -2887,6 +3268,9 @@ int32_t run_linears(const uint16_t* x, int64_t m, int64_t k, const LinearJob* jo
     } else if (path == LOGBQ_PATH_GEMV) {
       gl[ng++] = live[a];
       grows += j.n;
+    } else if (path == LOGBQ_PATH_MFMA_PF) {
+      const int32_t r = launch_pf<BITS>(x, M, K, j, st, cus);
+      if (r != LOGBQ_OK) return r;
     } else if (path == LOGBQ_PATH_MFMA_KQ) {
       const int32_t r = BITS == 8 ? launch_kq8(x, M, K, j, st) : launch_kq(x, M, K, j, st);
       if (r != LOGBQ_OK) return r;
@@ -3365,6 +3749,9 @@ int32_t logbq_linear_kernel(int32_t bits, int64_t m, int64_t k, int64_t n, const
       const int nbuf = (cpl <= 2 && M <= 2) ? 3 : 2;
       std::snprintf(buf, sizeof(buf), "k_gemv<%d, %d, %d, %s, %d>", bits, M, cpl,
                     wk > 1 ? "true" : "false", nbuf);
+    } else if (path == LOGBQ_PATH_MFMA_PF) {
+      std::snprintf(buf, sizeof(buf), "k_mfma_pf<%d, %d>", bits,
+                    pf_config(M, n, K, bits).bt);
     } else if (path == LOGBQ_PATH_MFMA_KQ && bits == 8) {
       std::snprintf(buf, sizeof(buf), "k_mfma_kq8");
     } else if (path == LOGBQ_PATH_MFMA_KQ && symmetric) {

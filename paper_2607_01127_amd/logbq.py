@@ -298,7 +298,7 @@ def dequantize8(codes, codebook, out=None, stream=None):
     return out
 
 
-PATH_NAMES = {0: "none", 1: "gemv", 2: "mfma", 3: "splitk", 4: "mfma_kq"}
+PATH_NAMES = {0: "none", 1: "gemv", 2: "mfma", 3: "splitk", 4: "mfma_kq", 5: "mfma_pf"}
 
 
 def linear_path(bits: int, m: int, k: int, n: int) -> str:

@@ -92,3 +92,38 @@ def test_gptq_edges(n, k, book, special):
     assert np.array_equal(got, codes_ref[:, 0::2] | (codes_ref[:, 1::2] << 4))
     same = (wg.view(np.uint32) == w_ref.view(np.uint32)) | (np.isnan(wg) & np.isnan(w_ref))
     assert same.all(), f"{np.count_nonzero(~same)} of {same.size} weights differ"
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("n,k,m", [(16640, 32, 257), (16385, 96, 320), (16383, 544, 513),
+                                   (4097, 1056, 2049), (14336, 64, 1024), (4096, 14336, 1025)])
+def test_prefill_tiles(bits, n, k, m):
+    """Prefill tiles of 256 weight rows x 64 to 256 batch rows and steps of 64 k: one row past a
+    tile, one short of it, part steps, one and two K parts; a fitted-like and an arbitrary codebook
+    against float64, y prefilled with NaN, the buffer behind it as it was, two calls bit-equal. The
+    bound is the rounding of a codebook entry to float16, 2^-11, plus k float32 sums."""
+    assert L.linear_path(bits, m, k, n) == "mfma_pf"
+    print(f"prefill bits={bits} n={n} k={k} m={m} {L.linear_kernel(bits, m, k, n)}", flush=True)
+    rng = np.random.default_rng([bits, n, k, m])
+    c = torch.from_numpy(rng.integers(0, 256, size=(n, k * bits // 8), dtype=np.uint8)).to(DEV)
+    x = torch.from_numpy(rng.standard_normal((m, k)).astype(np.float16)).to(DEV)
+    half = (1 << (bits - 1)) - 1
+    mag = np.concatenate([[0], 1.5 ** (np.linspace(-6, 0, half))])
+    pick = rng.choice(m, 40, replace=False)
+    pick[:2] = 0, m - 1
+    for book in (np.concatenate([mag, -mag]), rng.standard_normal(1 << bits)):
+        book = book.astype(np.float32)
+        buf = torch.full((m * n + 64,), float("nan"), device=DEV)
+        buf[m * n:] = 7.0
+        y = buf[:m * n].view(m, n)
+        call = L.linear if bits == 4 else L.linear8
+        call(x, c, book, out=y)
+        y2 = call(x, c, book)
+        assert torch.equal(y, y2) and bool((buf[m * n:] == 7.0).all())
+        table = torch.tensor(book.astype(np.float64), device=DEV)
+        w = table[c.int()] if bits == 8 else torch.stack(
+            [table[(c & 15).int()], table[(c >> 4).int()]], dim=2).reshape(n, k)
+        xs = x[torch.from_numpy(pick).to(DEV)].double()
+        bound = (xs.abs() @ w.abs().T.contiguous()) * (2.0 ** -11 + k * 2.0 ** -24)
+        got = y[torch.from_numpy(pick).to(DEV)].double()
+        assert bool(((got - xs @ w.T.contiguous()).abs() <= bound).all())
