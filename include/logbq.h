@@ -330,7 +330,8 @@ typedef enum logbq_path {
   LOGBQ_PATH_MFMA = 2,     /* stepped dequantize-into-MFMA skinny GEMM                        */
   LOGBQ_PATH_SPLITK = 3,   /* split-K dequantize-into-MFMA kernel (4-bit, 2 <= m <= 32; 8-bit,
                               3 <= m <= 16); above m = 16 a 4-bit codebook that is not
-                              sign-symmetric runs the stepped kernel instead                  */
+                              sign-symmetric runs the stepped kernel instead, and where k is
+                              not 1, 2, 4, 8 or 14 Ki the GEMV or the stepped kernel          */
   LOGBQ_PATH_MFMA_KQ = 4,  /* K-quartered dequantize-into-MFMA GEMM (4-bit, m > 96, n >= 4096;
                               8-bit, m > 64, n >= 16384); a 4-bit codebook that is not
                               sign-symmetric (never a fitted one) runs the stepped kernel     */

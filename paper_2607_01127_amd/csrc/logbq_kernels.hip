@@ -17,7 +17,7 @@
 //              workgroup share a block of 16 rows (one K slice each, activations held in
 //              registers) and sum their partial tiles through LDS; at K = 8192 and m > 16, on
 //              narrow layers, and at K = 14336, two workgroups share a block (one K half each)
-//              and add into a zeroed y.
+//              and add into a zeroed y. k_mfma_skr: the same at any other K, m <= 16.
 //   k_mfma_sk8 the split-K product on 8-bit codes (m <= 16), weights looked up in an LDS table.
 //   k_mfma_kq  the same product for m > 96: each wavefront takes 64 weight rows and one K
 //              quarter of every step for all 128 batch rows of the workgroup; the quarters'
@@ -2068,15 +2068,19 @@ struct SkSegs {
   SkSeg s[kMaxSegs];
 };
 
-template <int ND, int WAVES, int G, int T, int KS, bool PAIRS>
-__global__ __launch_bounds__(64 * WAVES) void k_mfma_sk(const uint16_t* __restrict__ x,
-                                                 const uint8_t* codes0, int n_rows0, int nseg,
-                                                 int nblocks, int k_cols, int m_rows,
-                                                 SkSegs segs, Lut16 lut) {
+// RAG serves any other K: the launch has as many wavefronts as K needs (at most WAVES), each K
+// part holds wavefronts x 32 ND columns, and what lies past the end of a row is neither read nor
+// added (zero activations meet zero codes).
+template <int ND, int WAVES, int G, int T, int KS, bool PAIRS, bool RAG>
+__device__ __forceinline__ void mfma_sk_body(const uint16_t* __restrict__ x,
+                                             const uint8_t* codes0, int n_rows0, int nseg,
+                                             int nblocks, int k_cols, int m_rows,
+                                             const SkSegs segs, const Lut16 lut) {
   static_assert(ND == 4 || ND == 8 || ND == 16 || ND == 32, "64 / ND rows per load");
   static_assert(G == 1 || G == 2 || G == 4, "batch groups");
-  static_assert((T == 1 || (T == 2 && G == 1 && !PAIRS)) && (KS == 1 || (KS == 2 && !PAIRS)),
-                "two batch tiles and the K split only with register tables");
+  static_assert((T == 1 || (T == 2 && G == 1 && !PAIRS)) && (KS == 1 || (KS == 2 && !PAIRS)) &&
+                    (!RAG || (T == 1 && !PAIRS)),
+                "two batch tiles, the K split and ragged K only with register tables");
   constexpr int BR = 16 * ND;            // code bytes per row per wavefront and block
   constexpr int RPI = 64 / ND;           // rows per load instruction
   constexpr int NI = ND / 4;             // load instructions per block
@@ -2100,8 +2104,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_mfma_sk(const uint16_t* __restri
   const int part = KS == 2 ? (int)(blockIdx.x & 1) : 0;
   const int gb = (int)gridDim.x / KS;
   const int b0 = (int)blockIdx.x / KS;
-  const int slice_k0 = part * (k_cols / KS) + w * 32 * ND;
-  const int slice_b0 = part * (int)(row_bytes / KS) + w * BR;
+  const int nw = RAG ? (int)blockDim.x >> 6 : WAVES;
+  const int part_k = RAG ? nw * 32 * ND : k_cols / KS;
+  const int slice_k0 = part * part_k + w * 32 * ND;
+  const int slice_b0 = slice_k0 / 2;
   // The fields of the segment that holds block b, selected with static indices: a field read
   // at a run-time segment index compiles to a vector load from the argument block, and its
   // wait would also wait for every code load in flight.
@@ -2130,13 +2136,17 @@ __global__ __launch_bounds__(64 * WAVES) void k_mfma_sk(const uint16_t* __restri
   for (int tt = 0; tt < T; ++tt) {
     const int mrow = 16 * tt + j % MB, sg = j / MB;
     const bool live = mrow < m_rows;
-    const int64_t base = (int64_t)(live ? mrow : 0) * k_cols + slice_k0 + 8 * ND * g;
-#pragma unroll
-    for (int r = 0; r < XR; ++r)
-      xa[tt][r] = *reinterpret_cast<const u32x4*>(x + base + 8 * (G * r + sg));
+    const int64_t row0 = (int64_t)(live ? mrow : 0) * k_cols;
+    const int k0 = slice_k0 + 8 * ND * g;
 #pragma unroll
     for (int r = 0; r < XR; ++r) {
-      u32x4 v = live ? xa[tt][r] : u32x4{0u, 0u, 0u, 0u};
+      const int k = k0 + 8 * (G * r + sg);
+      xa[tt][r] = *reinterpret_cast<const u32x4*>(x + row0 + (!RAG || k < k_cols ? k : 0));
+    }
+#pragma unroll
+    for (int r = 0; r < XR; ++r) {
+      const bool in = live && (!RAG || k0 + 8 * (G * r + sg) < k_cols);
+      u32x4 v = in ? xa[tt][r] : u32x4{0u, 0u, 0u, 0u};
       xa[tt][r] = PAIRS ? v : permute_x8(v);
     }
   }
@@ -2160,13 +2170,19 @@ __global__ __launch_bounds__(64 * WAVES) void k_mfma_sk(const uint16_t* __restri
 #pragma unroll
     for (int c = 0; c < NI; ++c) {
       const int r = RPI * c + lane / ND;
-      const int off = r * (int)row_bytes + slice_b0 + 16 * (lane % ND);
+      int off = r * (int)row_bytes + slice_b0 + 16 * (lane % ND);
+      // (an offset past the end of the descriptor reads as zeros)
+      if (RAG && slice_b0 + 16 * (lane % ND) >= (int)row_bytes) off = (int)0x80000000u;
       q[c] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kCachePolicyNT);
     }
   };
   u32x4 q[2][NI];
   load_block(b0, q[0]);
   if constexpr (PAIRS) fill_lut<4, NT>(s_lut, lut);
+  if constexpr (RAG) {                 // partial tiles of wavefronts that the launch leaves out
+    for (int i = nw * 64 + t; i < WAVES * 64; i += nw * 64)
+      s_red[0][i >> 6][0][i & 63] = s_red[1][i >> 6][0][i & 63] = float4v{0.f, 0.f, 0.f, 0.f};
+  }
   __syncthreads();
 
   float res[NRES];
@@ -2273,6 +2289,24 @@ __global__ __launch_bounds__(64 * WAVES) void k_mfma_sk(const uint16_t* __restri
     if (b + gb < nblocks) block(b + gb, q[1]);
   }
   flush();
+}
+
+template <int ND, int WAVES, int G, int T, int KS, bool PAIRS>
+__global__ __launch_bounds__(64 * WAVES) void k_mfma_sk(const uint16_t* __restrict__ x,
+                                                 const uint8_t* codes0, int n_rows0, int nseg,
+                                                 int nblocks, int k_cols, int m_rows,
+                                                 SkSegs segs, Lut16 lut) {
+  mfma_sk_body<ND, WAVES, G, T, KS, PAIRS, false>(x, codes0, n_rows0, nseg, nblocks, k_cols,
+                                                  m_rows, segs, lut);
+}
+
+template <int ND, int G, int KS>
+__global__ __launch_bounds__(1024) void k_mfma_skr(const uint16_t* __restrict__ x,
+                                                 const uint8_t* codes0, int n_rows0, int nseg,
+                                                 int nblocks, int k_cols, int m_rows,
+                                                 SkSegs segs, Lut16 lut) {
+  mfma_sk_body<ND, 16, G, 1, KS, false, true>(x, codes0, n_rows0, nseg, nblocks, k_cols, m_rows,
+                                              segs, lut);
 }
 
 // ------------------------------------------------------------------ split-K MFMA, 8-bit codes
@@ -3051,6 +3085,22 @@ bool sk_shape(int M, int K) {
                     (M <= 16 && K == 14336));
 }
 
+// Split-K at any other K (k_mfma_skr): 4-bit codes of sign-symmetric codebooks (any other codebook
+// takes the kernel that the remaining rules name), 512 <= K <= 16384. Where it is the faster
+// (MI355X, graph replay, codes streamed from HBM; GEMV up to m = 8, stepped kernel above -> split-K):
+// m = 3 from N = 4096 (1024 x 5120 4.6 -> 6.0 us, 4096 x 5120 7.4 -> 6.4, 13824 x 5120 17.6 -> 12.2);
+// m = 4, 5 above N = 1024 (1024 x 11008 at m = 5 7.9 -> 8.4, 2048 x 2560 5.4 -> 4.7, 4096 x 11008
+// 18.8 -> 10.9); m = 6 .. 8 everywhere (1024 x 3072 at m = 8 6.8 -> 5.1, 4096 x 11008 26.9 -> 11.2,
+// 8192 x 7168 29.6 -> 12.1); above m = 8 up to N = 8192 at K <= 4096 (m = 16: 8192 x 3072
+// 10.0 -> 9.3, 16000 x 3072 10.8 -> 12.3), else up to N = 4096 (m = 12: 4096 x 11008 17.2 -> 14.9,
+// 8192 x 7168 13.8 -> 15.1) and above m = 12 up to N = 2048 (m = 16: 2048 x 7168 12.5 -> 11.5,
+// 4096 x 11008 17.3 -> 17.9). From N = 16384 the stepped kernel has a workgroup for every other CU.
+bool skr_shape(int M, int64_t N, int K) {
+  if (M < 3 || M > 16 || N >= 16384 || K < 512 || K > 16384 || sk_shape(M, K)) return false;
+  if (M <= 8) return M >= 6 || (M >= 4 ? N > 1024 : N >= 4096);
+  return N <= (K <= 4096 ? 8192 : M <= 12 ? 4096 : 2048);
+}
+
 // Split-K configuration: code dwords per lane and row, wavefronts per workgroup, batch groups,
 // batch tiles and K parts (workgroups per block).
 struct SkConfig {
@@ -3064,6 +3114,12 @@ struct SkConfig {
 // and the codebook's kind, so a grouped launch only joins linears of equal configuration and
 // each computes as in a call of its own.
 SkConfig sk_config(int M, int K, bool pairs, int blocks) {
+  if (!sk_shape(M, K)) {   // any other K: the same sizes, as many wavefronts as K needs
+    const bool narrow = K > 4096 && blocks <= (M <= 8 ? 128 : 512);
+    const int kparts = K > 8192 || narrow ? 2 : 1, per = (K + kparts - 1) / kparts;
+    const int nd = per > 4096 ? 16 : per > 1024 ? 8 : 4;
+    return {nd, (per + 32 * nd - 1) / (32 * nd), M <= 8 ? 2 : 1, 1, kparts};
+  }
   // K = 14336 = 2 x 14 x 512: workgroup pairs of 14 wavefronts, one K half each.
   if (K == 14336) return {16, 14, M <= 8 ? 2 : 1, 1, 2};
   if (M > 16) {   // two batch tiles (register tables only); K = 8192 over workgroup pairs
@@ -3121,6 +3177,20 @@ int32_t launch_sk(const uint16_t* x, int M, int K, const LinearJob* jobs, const 
                        st, x, sgs.s[0].codes, sgs.s[0].n_rows, nseg, nblocks, K, M, sgs, l);     \
     return launch_status();                                                                      \
   }
+    if (!sk_shape(M, K)) {
+#define LOGBQ_SKR(ND, GG, KP)                                                                    \
+  if (c.nd == ND && c.groups == GG && c.kparts == KP) {                                          \
+    hipLaunchKernelGGL((k_mfma_skr<ND, GG, KP>), dim3((unsigned)grid),                           \
+                       dim3(64u * (unsigned)c.waves), 0, st, x, sgs.s[0].codes,                  \
+                       sgs.s[0].n_rows, nseg, nblocks, K, M, sgs, l);                            \
+    return launch_status();                                                                      \
+  }
+      LOGBQ_SKR(4, 1, 1) LOGBQ_SKR(4, 2, 1) LOGBQ_SKR(8, 1, 1) LOGBQ_SKR(8, 2, 1)
+      LOGBQ_SKR(16, 1, 1) LOGBQ_SKR(16, 2, 1) LOGBQ_SKR(8, 1, 2) LOGBQ_SKR(8, 2, 2)
+      LOGBQ_SKR(16, 1, 2) LOGBQ_SKR(16, 2, 2)
+#undef LOGBQ_SKR
+      return LOGBQ_ERR_UNSUPPORTED;
+    }
     LOGBQ_SK(4, 8, 1, 1, 1, true) LOGBQ_SK(8, 8, 1, 1, 1, true)
     LOGBQ_SK(16, 8, 1, 1, 1, true) LOGBQ_SK(32, 8, 1, 1, 1, true)
     LOGBQ_SK(4, 8, 1, 1, 1, false) LOGBQ_SK(4, 8, 2, 1, 1, false)
@@ -3212,7 +3282,7 @@ int32_t launch_sk(const uint16_t* x, int M, int K, const LinearJob* jobs, const 
 // over N = 1024 .. 28672, K = 2048 .. 8192: e.g. 4096 x 4096 at m = 8: 7.3 us vs 12.9 us for the
 // GEMV; 8192 -> 28672 at m = 5: 40.9 vs 90.7 us; N = 1024, K = 8192 at m = 8: 9.9 vs 8.4 us).
 template <int BITS>
-int choose_path(int M, int K, int64_t N) {
+int choose_path(int M, int K, int64_t N, bool symmetric = true) {
   int wk = 0, cpl = 0;
   if (BITS == 8 && sk8_shape(M, K) &&
       ((M >= 5 && M <= 8 && !(N <= 1024 && K >= 4096)) || (M <= 4 && M >= 3 && N >= 8192) ||
@@ -3222,6 +3292,7 @@ int choose_path(int M, int K, int64_t N) {
       ((M >= 5 && M <= 16) || (M == 4 && (N > 1024 || K <= 4096)) || (M == 3 && N >= 4096) ||
        (M > 16 && (K <= 4096 || N <= 16384 || M <= 20))))
     return LOGBQ_PATH_SPLITK;
+  if (BITS == 4 && symmetric && skr_shape(M, N, K)) return LOGBQ_PATH_SPLITK;
   if (M <= 8 && gemv_config<BITS>(M, K, &wk, &cpl) &&
       !(M >= (BITS == 8 ? 5 : 3) && (int64_t)M * N > 65536))
     return LOGBQ_PATH_GEMV;
@@ -3259,7 +3330,11 @@ int32_t run_linears(const uint16_t* x, int64_t m, int64_t k, const LinearJob* jo
   int ns = 0;
   for (int a = 0; a < nlive; ++a) {
     const LinearJob& j = jobs[live[a]];
-    const int path = choose_path<BITS>(M, K, j.n);
+    LutBytes tb;
+    float scale;
+    const bool symmetric = BITS == 8 || !skr_shape(M, j.n, K) ||
+                           make_lut_bytes(j.codebook, &tb, &scale);
+    const int path = choose_path<BITS>(M, K, j.n, symmetric);
     if (path == LOGBQ_PATH_SPLITK && BITS == 8) {
       const int32_t r = launch_sk8(x, M, K, j, st, cus);
       if (r != LOGBQ_OK) return r;
@@ -3734,14 +3809,17 @@ int32_t logbq_linear_kernel(int32_t bits, int64_t m, int64_t k, int64_t n, const
     LutBytes tb;
     float scale;
     const bool symmetric = bits == 4 && (!codebook || make_lut_bytes(codebook, &tb, &scale));
-    const int path = bits == 4 ? choose_path<4>(M, K, n) : choose_path<8>(M, K, n);
+    const int path = bits == 4 ? choose_path<4>(M, K, n, symmetric) : choose_path<8>(M, K, n);
     int wk = 0, cpl = 0;
     if (path == LOGBQ_PATH_SPLITK && bits == 8) {
       std::snprintf(buf, sizeof(buf), "k_mfma_sk8<%d, %d>", K / 512, M <= 8 ? 2 : 1);
     } else if (path == LOGBQ_PATH_SPLITK && ((M <= 16 && K != 14336) || symmetric)) {
       const SkConfig c = sk_config(M, K, !symmetric, (int)((n + 15) / 16));
-      std::snprintf(buf, sizeof(buf), "k_mfma_sk<%d, %d, %d, %d, %d, %s>", c.nd, c.waves,
-                    c.groups, c.tiles, c.kparts, symmetric ? "false" : "true");
+      if (!sk_shape(M, K))
+        std::snprintf(buf, sizeof(buf), "k_mfma_skr<%d, %d, %d>", c.nd, c.groups, c.kparts);
+      else
+        std::snprintf(buf, sizeof(buf), "k_mfma_sk<%d, %d, %d, %d, %d, %s>", c.nd, c.waves,
+                      c.groups, c.tiles, c.kparts, symmetric ? "false" : "true");
     } else if (path == LOGBQ_PATH_GEMV) {
       const bool ok = bits == 4 ? gemv_config_rows<4>(M, K, n, &wk, &cpl)
                                 : gemv_config_rows<8>(M, K, n, &wk, &cpl);

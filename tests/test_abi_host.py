@@ -409,3 +409,16 @@ def test_prefill_path_rule():
     assert lp(4, 300, 1 << 22, 28672) != "mfma_pf" and lp(4, 300, 4096, 1 << 21) != "mfma_pf"
     for bits in (4, 8):
         assert lk(bits, 2048, 4096, 14336, np.arange(1 << bits, dtype=np.float32)).startswith("k_mfma_pf<")
+
+
+def test_ragged_split_k_rule():
+    """Split-K outside its powers of two: fitted 4-bit codebooks, 3 <= m <= 16, n < 16384; another
+    codebook takes the kernel that the remaining rules name."""
+    lp, lk = L.linear_path, L.linear_kernel
+    assert lp(4, 8, 11008, 4096) == "splitk" and lk(4, 8, 11008, 4096) == "k_mfma_skr<16, 2, 2>"
+    assert lk(4, 16, 3072, 1000) == "k_mfma_skr<8, 1, 1>" and lk(4, 6, 544, 64) == "k_mfma_skr<4, 2, 1>"
+    assert lk(4, 4, 5120, 2048) == "k_mfma_skr<8, 2, 2>" and lk(4, 4, 5120, 2049) == "k_mfma_skr<16, 2, 1>"
+    assert lp(4, 2, 11008, 4096) == "gemv" and lp(4, 3, 11008, 4095) == "gemv"
+    assert lp(4, 17, 11008, 4096) == "mfma" and lp(4, 8, 3072, 16384) == "mfma"
+    assert lp(4, 9, 16416, 1024) == "mfma" and lp(4, 8, 480, 64) == "gemv"
+    assert lk(4, 8, 11008, 4096, np.arange(16, dtype=np.float32)) == "k_gemv<4, 8, 1, true, 2>"

@@ -127,3 +127,37 @@ def test_prefill_tiles(bits, n, k, m):
         bound = (xs.abs() @ w.abs().T.contiguous()) * (2.0 ** -11 + k * 2.0 ** -24)
         got = y[torch.from_numpy(pick).to(DEV)].double()
         assert bool(((got - xs @ w.T.contiguous()).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("n,k", [(130, 512), (33, 1056), (40, 4128), (4097, 4064), (2047, 8160),
+                                 (2049, 8224), (1025, 11008), (4099, 16352)])
+def test_ragged_split_k(n, k):
+    """Split-K at K outside its powers of two: a last wavefront with one column block of 32 or all
+    but one, one and two K parts, a partial last block of rows. Single calls repeat their bits, a
+    grouped call equals them, and another codebook (which takes another kernel) agrees too, all
+    within the float16 rounding of the codebook, 2^-11, plus k float32 sums."""
+    rng = np.random.default_rng([n, k])
+    c = torch.from_numpy(rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8)).to(DEV)
+    mag = np.concatenate([[0], 1.5 ** np.linspace(-6, 0, 7)])
+    books = [np.concatenate([mag, -mag]).astype(np.float32),
+             rng.standard_normal(16).astype(np.float32)]
+    for m in (3, 4, 6, 8, 9, 16):
+        print(f"ragged split-K n={n} k={k} m={m} {L.linear_kernel(4, m, k, n)}", flush=True)
+        x = torch.from_numpy(rng.standard_normal((m, k)).astype(np.float16)).to(DEV)
+        ys = []
+        for book in books:
+            y = torch.full((m, n), float("nan"), device=DEV)
+            L.linear(x, c, book, out=y)
+            assert torch.equal(y, L.linear(x, c, book))
+            table = torch.tensor(book.astype(np.float64), device=DEV)
+            w = torch.stack([table[(c & 15).int()], table[(c >> 4).int()]], dim=2).reshape(n, k)
+            bound = (x.double().abs() @ w.abs().T.contiguous()) * (2.0 ** -11 + k * 2.0 ** -24)
+            assert bool(((y.double() - x.double() @ w.T.contiguous()).abs() <= bound).all())
+            ys.append(y)
+        for a, b in zip(L.linear_multi(x, [c, c], books), ys):
+            assert torch.equal(a, b)
+        for a, b in zip(L.linear_multi(x, [c, c[:16]], [books[0]] * 2), (ys[0], None)):
+            if b is not None:
+                assert torch.equal(a, b)
+            else:
+                assert torch.equal(a, L.linear(x, c[:16], books[0]))
