@@ -2460,47 +2460,53 @@ __global__ __launch_bounds__(1024) void k_mfma_sk8(const uint16_t* __restrict__ 
 // [g C, (g + 1) C), C = fit_chunk(PASS, n, CUs), and accumulates per bin, in LDS, the count and the
 // integer sums of (m^2 >> 24) and (m^2 & 0xFFFFFF) of the weights the pass selects (m = integer
 // significand of |w|, m^2 < 2^48). The LDS word a holds count << 44 | sum of (m^2 >> 24): at
-// most C <= 2^19 weights per workgroup keep the sum below 2^43 and the count below 2^20, so one
-// 64-bit add updates both. Pass 1, which adds every weight, keeps two copies of its bins (even
-// and odd lanes), halving the lanes of one instruction that hit the same LDS word; its 64 KiB
-// then fit two workgroups per CU, so its chunks are twice as long and the grid runs in one
-// round (measured on the 8192 x 28672 weights: the fit 0.868 -> 0.840 ms). Passes 2 and 3 keep
-// chunks of 2^18: longer ones halve the bins they flush but leave half the workgroups to
-// stream, which measured slower. Non-empty bins are then added to the global bins with 64-bit
-// integer atomics, which are exact and independent of order. Pass 1 also takes the largest bit
-// pattern and flags NaN / Inf.
-constexpr int64_t kFitChunk = int64_t(1) << 18;
-constexpr int kFitThreads = 512;
-// Largest chunk of a pass: the bound that keeps every LDS word of a workgroup below overflow.
-constexpr int64_t fit_chunk_max(int pass) { return pass == 1 ? 2 * kFitChunk : kFitChunk; }
+// most 2^19 weights per word keep the sum below 2^43 and the count below 2^20, so one 64-bit add
+// updates both. Non-empty bins are then added to the global bins with 64-bit integer atomics,
+// which are exact and independent of order. Pass 1 also takes the largest bit pattern and flags
+// NaN / Inf.
+//
+// What bounds it: pass 1 adds every weight, and most weights share a few tens of bins, so the
+// lanes of an instruction wait for one another at the same LDS word; the passes before the last
+// also wait for their flush, three atomics per bin and workgroup on the same global words. Passes
+// 1 and 2 run one workgroup of 1024 threads per CU (a half and a quarter of the flushes) with four
+// copies of the bins, one per lane modulo 4 and interleaved, so that the copies of a bin lie on
+// different banks. A copy then takes a quarter of the weights, and a workgroup up to 2^20 of them.
+// 14336 x 4096 weights: pass 1 79 -> 66 us, pass 2 94 -> 52 us against 512 threads, 512 and 1024
+// workgroups and two copies side by side or one.
+// Pass 3 selects almost nothing and streams: workgroups of 512 threads, four per CU, one copy.
+constexpr int fit_threads(int pass) { return pass == 3 ? 512 : 1024; }
+constexpr int fit_copies(int pass) { return pass == 3 ? 1 : 4; }
+// Largest chunk of a pass: the bound that keeps every LDS word of a workgroup below overflow
+// (2^19 a copy would do in pass 3 too; half of it leaves no CU idle at the end).
+constexpr int64_t fit_chunk_max(int pass) { return int64_t(1) << (pass == 3 ? 18 : 20); }
 // Chunk of a pass over n weights: the largest chunk, or less for tensors too small to give
-// every CU its share (about two workgroups per CU in pass 1, four in passes 2 and 3), in
-// multiples of 4096 weights. Measured on MI355X: the 4096 x 1024 projections of a decode layer
-// ran pass 1 on 8 workgroups (140 us) with the largest chunk.
+// every CU its share, in multiples of 4096 weights. Measured on MI355X: the 4096 x 1024
+// projections of a decode layer ran pass 1 on 8 workgroups (140 us) with the largest chunk.
 int64_t fit_chunk(int pass, int64_t n, int cus) {
-  const int64_t target = (int64_t)cus * (pass == 1 ? 2 : 4);
+  const int64_t target = (int64_t)cus * (pass == 3 ? 4 : 1);
   int64_t c = (n + target - 1) / target;
   c = (c + 4095) / 4096 * 4096;
   return c < fit_chunk_max(pass) ? c : fit_chunk_max(pass);
 }
 
 template <int PASS>
-__global__ __launch_bounds__(kFitThreads) void k_fit_hist(const float* __restrict__ w, int64_t n,
+__global__ __launch_bounds__(fit_threads(PASS)) void k_fit_hist(const float* __restrict__ w, int64_t n,
                                                          int64_t C, uint32_t sel,
                                                          unsigned long long* __restrict__ bins,
                                                          unsigned int* __restrict__ flags) {
   constexpr int NB = PASS == 1 ? logbq_detail::kFitBins1
                      : PASS == 2 ? logbq_detail::kFitBins2 : logbq_detail::kFitBins3;
-  constexpr int REP = PASS == 1 ? 2 : 1;
+  constexpr int kThreads = fit_threads(PASS);
+  constexpr int REP = fit_copies(PASS);
   __shared__ unsigned long long s_a[REP * NB];
   __shared__ unsigned long long s_c[REP * NB];
   __shared__ unsigned int s_max, s_bad;
   const int t = threadIdx.x;
-  for (int i = t; i < REP * NB; i += kFitThreads) {
+  for (int i = t; i < REP * NB; i += kThreads) {
     s_a[i] = 0;
     s_c[i] = 0;
   }
-  const int rep = REP == 1 ? 0 : (t & 1) * NB;
+  const uint32_t rep = (uint32_t)t % REP;
   if (t == 0) {
     s_max = 0;
     s_bad = 0;
@@ -2526,8 +2532,8 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_hist(const float* __restric
     if (take) {
       const uint64_t m = (key & 0x7FFFFFu) | (key >= 0x800000u ? 0x800000u : 0u);
       const uint64_t q = m * m;
-      atomicAdd(&s_a[rep + bin], (1ull << 44) | (q >> 24));
-      atomicAdd(&s_c[rep + bin], (unsigned long long)(q & 0xFFFFFFu));
+      atomicAdd(&s_a[bin * REP + rep], (1ull << 44) | (q >> 24));
+      atomicAdd(&s_c[bin * REP + rep], (unsigned long long)(q & 0xFFFFFFu));
     }
   };
   const int64_t begin = (int64_t)blockIdx.x * C;   // C <= fit_chunk_max(PASS), a multiple of 4
@@ -2538,17 +2544,17 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_hist(const float* __restric
   // flight per thread left HBM idle: 263 -> 244 us and 196 -> 182 us per pass on the
   // 8192 x 28672 tensor, MI355X); pass 3 bins almost nothing and streams best with U = 1.
   constexpr int U = PASS == 3 ? 1 : 4;
-  for (int64_t i0 = begin + 4 * t; i0 < vend; i0 += 4 * kFitThreads * U) {
+  for (int64_t i0 = begin + 4 * t; i0 < vend; i0 += 4 * kThreads * U) {
     u32x4 v[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-      const int64_t i = i0 + (int64_t)j * 4 * kFitThreads;
+      const int64_t i = i0 + (int64_t)j * 4 * kThreads;
       v[j] = i < vend ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(w + i))
                       : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-      if (i0 + (int64_t)j * 4 * kFitThreads < vend) {
+      if (i0 + (int64_t)j * 4 * kThreads < vend) {
         add(v[j].x);
         add(v[j].y);
         add(v[j].z);
@@ -2562,13 +2568,13 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_hist(const float* __restric
     if (bad) atomicOr(&s_bad, 1u);
   }
   __syncthreads();
-  for (int i = t; i < NB; i += kFitThreads) {
+  for (int i = t; i < NB; i += kThreads) {
     unsigned long long cnt = 0, hi = 0, lo = 0;
     for (int r = 0; r < REP; ++r) {
-      const unsigned long long a = s_a[r * NB + i];
+      const unsigned long long a = s_a[i * REP + r];
       cnt += a >> 44;
       hi += a & ((1ull << 44) - 1);
-      lo += s_c[r * NB + i];
+      lo += s_c[i * REP + r];
     }
     if (cnt == 0) continue;
     atomicAdd(&bins[3 * i], cnt);
@@ -3468,17 +3474,17 @@ int32_t fit_device_pass(void* vctx, int pass, uint32_t sel, logbq_detail::FitPas
   if (pass == 1) {
     off = 0;   // the flags are copied with pass 1's bins
     words = kFitOff2;
-    hipLaunchKernelGGL(k_fit_hist<1>, dim3(grid), dim3(kFitThreads), 0, c.st, c.w, c.n, chunk, sel,
+    hipLaunchKernelGGL(k_fit_hist<1>, dim3(grid), dim3(fit_threads(1)), 0, c.st, c.w, c.n, chunk, sel,
                        c.ws + kFitOff1, flags);
   } else if (pass == 2) {
     off = kFitOff2;
     words = kFitOff3 - kFitOff2;
-    hipLaunchKernelGGL(k_fit_hist<2>, dim3(grid), dim3(kFitThreads), 0, c.st, c.w, c.n, chunk, sel,
+    hipLaunchKernelGGL(k_fit_hist<2>, dim3(grid), dim3(fit_threads(2)), 0, c.st, c.w, c.n, chunk, sel,
                        c.ws + kFitOff2, flags);
   } else {
     off = kFitOff3;
     words = kFitWords - kFitOff3;
-    hipLaunchKernelGGL(k_fit_hist<3>, dim3(grid), dim3(kFitThreads), 0, c.st, c.w, c.n, chunk, sel,
+    hipLaunchKernelGGL(k_fit_hist<3>, dim3(grid), dim3(fit_threads(3)), 0, c.st, c.w, c.n, chunk, sel,
                        c.ws + kFitOff3, flags);
   }
   if (launch_status() != LOGBQ_OK) return LOGBQ_ERR_HIP;
