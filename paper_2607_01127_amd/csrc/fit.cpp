@@ -138,6 +138,15 @@ struct Big {
     }
     if (carry) d.push_back(uint32_t(carry));
   }
+  void sub(const Big& o) {  // this >= o
+    int64_t borrow = 0;
+    for (size_t i = 0; i < d.size(); ++i) {
+      const int64_t t = int64_t(d[i]) - (i < o.d.size() ? o.d[i] : 0u) + borrow;
+      d[i] = uint32_t(t);
+      borrow = t >> 32;   // 0 or -1
+    }
+    trim();
+  }
   Big mul(const Big& o) const {
     Big r;
     if (d.empty() || o.d.empty()) return r;
@@ -257,6 +266,34 @@ float exact_threshold(double b, int32_t s, int k, const Big& pw) {
     if (ge_half_power(g, b, n, pw)) f = g; else break;
   }
   return f;
+}
+
+// The same threshold from an interval: t^2 = b^n by repeated squaring in long double, whose
+// roundings (2^-64 each) add up to a relative error below |n| 2^-64, then one reciprocal and one
+// square root. If both ends of the interval round up to the same float32, that is the threshold
+// (its predecessor lies below the interval); false leaves the decision to the exact integers,
+// about once in 2^30 thresholds. 64-bit significands (x87) are assumed, and checked.
+bool interval_threshold(double b, int32_t s, int k, float* out) {
+  if (std::numeric_limits<long double>::digits < 64) return false;
+  const int64_t n = 2 * int64_t(k) + 1 - 2 * int64_t(s);
+  long double p = 1.0L, x = (long double)b;
+  for (int64_t e = n < 0 ? -n : n; e > 0; e >>= 1) {
+    if (e & 1) p *= x;
+    x *= x;
+  }
+  if (!std::isfinite(p)) return false;
+  const long double t = sqrtl(n < 0 ? 1.0L / p : p);
+  const long double d = ldexpl((long double)(n < 0 ? -n : n) + 16.0L, -64);
+  const long double lo = t * (1.0L - d), hi = t * (1.0L + d);
+  if (!(lo > 0.0L && hi <= (long double)FLT_MAX)) return false;
+  auto up = [](long double v) {
+    const float f = (float)v;
+    return (long double)f < v ? std::nextafter(f, std::numeric_limits<float>::infinity()) : f;
+  };
+  const float f = up(lo);
+  if (f != up(hi)) return false;
+  *out = f;
+  return true;
 }
 
 // Code of x under the asymmetric linear quantizer: round(x / s) - z with ties up, clamped.
@@ -418,6 +455,14 @@ int32_t finish_params(int32_t bits, double eps, double wmin, double wmax, int64_
   p.codebook[half] = 0.0f;
   const int nthr = (int)(sizeof(p.thresholds) / sizeof(p.thresholds[0]));
   for (int k = qmax; k < nthr; ++k) p.thresholds[k] = std::numeric_limits<float>::infinity();
+  // Big integers cost 1 us (4 bits) to 10 us (8 bits) per threshold, the interval 0.1 us.
+  bool sure = true;
+  for (int k = 0; sure && k < qmax; ++k)
+    sure = interval_threshold(b, p.shift, k, &p.thresholds[k]);
+  if (sure) {
+    *out = p;
+    return LOGBQ_OK;
+  }
   // B^|n_k| for n_k = 2k + 1 - 2s (odd, never 0). The k with n_k > 0 are taken upward from the
   // smallest such k, those with n_k < 0 downward from the largest: |n_k| grows by 2 per step
   // in both sweeps, so each sweep squares once and then multiplies by B^2 per step.
@@ -457,15 +502,23 @@ int32_t finish_params(int32_t bits, double eps, double wmin, double wmax, int64_
 
 namespace {
 
-// Energy of a bin in units of 2^-298 (the square of the smallest float32 subnormal):
-// (hi * 2^24 + lo) * 2^(2 ef + 298), where |w| = m * 2^ef for every weight of the bin.
-Big bin_energy(uint64_t hi, uint64_t lo, uint32_t exp_field) {
+typedef unsigned __int128 u128;
+
+// Energies are in units of 2^-298 (the square of the smallest float32 subnormal): a bin whose
+// weights are |w| = m * 2^ef has sum(m^2) 2^energy_shift(exp_field). The sum of m^2 over all bins
+// of one exponent stays below 2^88 (fewer than 2^40 weights), so it is kept in 128 bits and only
+// meets the long integers once per exponent.
+int64_t energy_shift(uint32_t exp_field) {
   const int64_t ef = exp_field == 0 ? -149 : int64_t(exp_field) - 150;
-  Big e(hi);
-  e.shl(24);
-  e.add(Big(lo));
-  e.shl(2 * ef + 298);
-  return e;
+  return 2 * ef + 298;
+}
+u128 bin_squares(const uint64_t* bin) { return (u128(bin[1]) << 24) + bin[2]; }
+void add_energy(Big& to, u128 squares, uint32_t exp_field) {
+  Big e(uint64_t(squares >> 64));
+  e.shl(64);
+  e.add(Big(uint64_t(squares)));
+  e.shl(energy_shift(exp_field));
+  to.add(e);
 }
 
 }  // namespace
@@ -486,8 +539,11 @@ int32_t fit_from_passes(int32_t bits, double eps, FitPassFn run, void* ctx, logb
   int64_t e;
   split_f64(eps, N, e);
   Big total;
-  for (int b = 0; b < kFitBins1; ++b)
-    if (r.bins[3 * b]) total.add(bin_energy(r.bins[3 * b + 1], r.bins[3 * b + 2], uint32_t(b) >> 3));
+  for (int b = 0; b < kFitBins1; b += 8) {
+    u128 squares = 0;
+    for (int i = b; i < b + 8; ++i) squares += bin_squares(r.bins + 3 * i);
+    if (squares) add_energy(total, squares, uint32_t(b) >> 3);
+  }
   Big target = total;
   target.mul_small(N);
   target.shr_ceil(-e);
@@ -497,16 +553,34 @@ int32_t fit_from_passes(int32_t bits, double eps, FitPassFn run, void* ctx, logb
   Big below;
   uint64_t count_below = 0;
   // First bin at which the running energy reaches the target; below / count_below then cover
-  // the bins before it.
+  // the bins before it. Per exponent, below + E 2^shift reaches the target iff
+  // E >= ceil((target - below) / 2^shift).
   auto pick = [&](const FitPassResult& pr, int nbins, uint32_t exp_field, bool per_bin_exp) {
-    for (int b = 0; b < nbins; ++b) {
-      const uint64_t* w = pr.bins + 3 * b;
-      if (w[0] == 0) continue;
-      Big run_e = below;
-      run_e.add(bin_energy(w[1], w[2], per_bin_exp ? uint32_t(b) >> 3 : exp_field));
-      if (reaches(run_e)) return b;
-      below.d.swap(run_e.d);
-      count_below += w[0];
+    const int group = per_bin_exp ? 8 : nbins;
+    for (int b0 = 0; b0 < nbins; b0 += group) {
+      bool any = false;
+      for (int b = b0; b < b0 + group; ++b) any |= pr.bins[3 * b] != 0;
+      if (!any) continue;
+      const uint32_t ef = per_bin_exp ? uint32_t(b0) >> 3 : exp_field;
+      Big gap = target;
+      gap.sub(below);
+      gap.shr_ceil(energy_shift(ef));
+      u128 need = 0;
+      if (gap.d.size() > 4) need = ~u128(0);
+      else for (size_t i = gap.d.size(); i-- > 0;) need = (need << 32) | gap.d[i];
+      u128 run_e = 0;
+      for (int b = b0; b < b0 + group; ++b) {
+        const uint64_t* w = pr.bins + 3 * b;
+        if (w[0] == 0) continue;
+        const u128 next = run_e + bin_squares(w);
+        if (next >= need) {
+          if (run_e) add_energy(below, run_e, ef);
+          return b;
+        }
+        run_e = next;
+        count_below += w[0];
+      }
+      if (run_e) add_energy(below, run_e, ef);
     }
     return -1;
   };
