@@ -335,7 +335,7 @@ typedef enum logbq_path {
   LOGBQ_PATH_MFMA_KQ = 4,  /* K-quartered dequantize-into-MFMA GEMM (4-bit, m > 96, n >= 4096;
                               8-bit, m > 64, n >= 16384); a 4-bit codebook that is not
                               sign-symmetric (never a fitted one) runs the stepped kernel     */
-  LOGBQ_PATH_MFMA_PF = 5   /* dequantize-into-MFMA GEMM of prefill, m > 256, k < 2^22         */
+  LOGBQ_PATH_MFMA_PF = 5   /* dequantize-into-MFMA GEMM of prefill, m > 128, k < 2^22         */
 } logbq_path;
 
 /*

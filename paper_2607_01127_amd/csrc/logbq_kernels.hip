@@ -22,7 +22,7 @@
 //   k_mfma_kq  the same product for m > 96: each wavefront takes 64 weight rows and one K
 //              quarter of every step for all 128 batch rows of the workgroup; the quarters'
 //              tiles are summed through LDS at the end (k_mfma_kq8: the same on 8-bit codes).
-//   k_mfma_pf  the same product for m > 256 (prefill): 256 weight rows x 64 to 256 batch rows per
+//   k_mfma_pf  the same product for m > 128 (prefill): 256 weight rows x 64 to 256 batch rows per
 //              workgroup, dequantization and staging issued between the MFMAs of the slice before.
 //   k_encode8, k_dequant8, k_gemv<8, ...>, k_mfma2<8, ...>  the same on 8-bit codes.
 //   k_encode_uniform  codes of the asymmetric linear baseline (Sec. 2), for comparisons.
@@ -3042,17 +3042,22 @@ PfCfg pf_config(int M, int64_t N, int K, int bits) {
   return best;
 }
 
-// The prefill kernel takes more than 256 batch rows unless the stepped kernel has a launch shape
+// The prefill kernel takes more than 128 batch rows unless the stepped kernel has a launch shape
 // that fits on the chip at once and its model's time, plus 5 us of launch and edges that the model
 // leaves out, is the shorter: narrow layers, whose 256-row tiles would leave most CUs idle
 // (1024 x 4096 at m = 300: 18.0 us against 27.1; 4096 x 4096 at m = 512: 34.6 against 41.6).
 // Elsewhere it replaces the K-quartered and the stepped kernels (4-bit 14336 x 4096 at m = 2048:
 // 316 -> 223 us, 8192 x 2048 at m = 600: 54 -> 34; another codebook 14336 x 4096 at m = 2048:
 // 410 -> 178; 8-bit 8199 x 3072 at m = 777: 173 -> 72, 14336 x 4096 at m = 2048: 698 -> 275).
+// Up to 256 rows the 4-bit K-quartered kernel keeps the layers that its grid covers in one round
+// (14336 x 4096 at m = 192: 44.8 us against 49.5; in two rounds 28672 x 2048: 55.1 -> 38.2, 28672 x
+// 8192: 167 -> 124), and the 8-bit one m = 129 .. 144, where its second row block stays in use and
+// under test (28672 x 8192 at m = 160: 263 -> 147).
 // k < 2^22 and n < 2^21 keep the descriptors over 256 rows of codes, of activations and of y
 // below 2^31 bytes, m n < 2^36 the one-dimensional grid below 2^32 threads.
 bool pf_shape(int M, int64_t N, int K, int bits) {
-  if (M <= 256 || K >= (1 << 22) || N >= (1 << 21) || M * N >= ((int64_t)1 << 36)) return false;
+  if (M <= 128 || K >= (1 << 22) || N >= (1 << 21) || M * N >= ((int64_t)1 << 36)) return false;
+  if (M <= 256 && (bits == 4 ? (N + 127) / 128 * 2 <= 256 : M <= 144)) return false;
   const double stepped = step_config(M, N, K, bits, true).cost;
   return stepped < 0.0 || pf_config(M, N, K, bits).cost < stepped + 5.0;
 }
@@ -3263,6 +3268,8 @@ int32_t launch_sk(const uint16_t* x, int M, int K, const LinearJob* jobs, const 
 // layer (8192 -> 28672 at m = 3 / 4: 48.0 / 56.1 us vs 57.2 / 57.3 us; at m = 6: 103 vs 57 us). The choice depends only on
 // (m, k, N), so every linear of a grouped call runs the kernel that a single call would run,
 // with the same result bits.
+//
+// Above m = 128 the prefill kernel takes what pf_shape says.
 //
 // Above m = 96 at N >= 4096 the K-quartered kernel replaces the stepped one for 4-bit codes with
 // sign-symmetric codebooks (7-11 % faster on the 8192 x 28672 and 4096 x 14336 layers; slower
