@@ -18,7 +18,8 @@
 //              registers) and sum their partial tiles through LDS; at K = 8192 and m > 16, on
 //              narrow layers, and at K = 14336, two workgroups share a block (one K half each)
 //              and add into a zeroed y. k_mfma_skr: the same at any other K, m <= 16.
-//   k_mfma_sk8 the split-K product on 8-bit codes (m <= 16), weights looked up in an LDS table.
+//   k_mfma_sk8 the split-K product on 8-bit codes (m <= 16), weights looked up in an LDS table
+//              (k_mfma_sk8r: any K up to 8192).
 //   k_mfma_kq  the same product for m > 96: each wavefront takes 64 weight rows and one K
 //              quarter of every step for all 128 batch rows of the workgroup; the quarters'
 //              tiles are summed through LDS at the end (k_mfma_kq8: the same on 8-bit codes).
@@ -2325,12 +2326,15 @@ __global__ __launch_bounds__(1024) void k_mfma_skr(const uint16_t* __restrict__ 
 // 4096 -> 14336 at m = 8: 28.1 -> 14.2 us, 8192 -> 2048 at m = 16: 48.8 -> 17.1 us; but
 // 8192 -> 28672 at m = 16: 57.9 -> 60.4 us, so m > 8 at K = 8192 and N > 16384 stays on the
 // stepped kernel.
-template <int ND, int G>
-__global__ __launch_bounds__(1024) void k_mfma_sk8(const uint16_t* __restrict__ x,
-                                                   const uint8_t* __restrict__ codes, int n_rows,
-                                                   int nblocks, int k_cols, int m_rows,
-                                                   float* __restrict__ y, float scale, Lut256 lut) {
-  static_assert(ND == 4 || ND == 8 || ND == 16, "K = 512 ND");
+//
+// RAG serves any other K up to 512 ND: what lies past the end of a row is neither read nor added.
+template <int ND, int G, bool RAG>
+__device__ __forceinline__ void mfma_sk8_body(const uint16_t* __restrict__ x,
+                                              const uint8_t* __restrict__ codes, int n_rows,
+                                              int nblocks, int k_cols, int m_rows,
+                                              float* __restrict__ y, float scale,
+                                              const Lut256& lut) {
+  static_assert(ND == 4 || ND == 8 || ND == 12 || ND == 16, "K = 512 ND");
   static_assert(G == 1 || G == 2, "batch groups");
   constexpr int W = 16;
   constexpr int NP = ND / 4;             // phases per block
@@ -2351,12 +2355,14 @@ __global__ __launch_bounds__(1024) void k_mfma_sk8(const uint16_t* __restrict__ 
   {
     const int mrow = j % MB, sg = j / MB;
     const bool live = mrow < m_rows;
-    const int64_t base = (int64_t)(live ? mrow : 0) * k_cols + slice0 + 32 * g;
+    const int64_t base = (int64_t)(live ? mrow : 0) * k_cols;
 #pragma unroll
     for (int r = 0; r < XR; ++r) {
       const int d = G * r + sg;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(x + base + 128 * (d >> 2) + 8 * (d & 3));
-      xa[r] = live ? v : u32x4{0u, 0u, 0u, 0u};
+      const int k = slice0 + 32 * g + 128 * (d >> 2) + 8 * (d & 3);
+      const bool in = !RAG || k < k_cols;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(x + base + (in ? k : 0));
+      xa[r] = live && in ? v : u32x4{0u, 0u, 0u, 0u};
     }
   }
   auto load_phase = [&](int b, int p, u32x4 (&q)[2]) {
@@ -2368,7 +2374,9 @@ __global__ __launch_bounds__(1024) void k_mfma_sk8(const uint16_t* __restrict__ 
         (void*)(codes + base), (short)0, size, kBufferRsrcWord3);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      const int off = (8 * c + (lane >> 3)) * k_cols + slice0 + 128 * p + 16 * (lane & 7);
+      int off = (8 * c + (lane >> 3)) * k_cols + slice0 + 128 * p + 16 * (lane & 7);
+      // (an offset past the end of the descriptor reads as zeros)
+      if (RAG && slice0 + 128 * p + 16 * (lane & 7) >= k_cols) off = (int)0x80000000u;
       q[c] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kCachePolicyNT);
     }
   };
@@ -2452,6 +2460,23 @@ __global__ __launch_bounds__(1024) void k_mfma_sk8(const uint16_t* __restrict__ 
     if (held == NRES) flush();
   }
   flush();
+}
+
+template <int ND, int G>
+__global__ __launch_bounds__(1024) void k_mfma_sk8(const uint16_t* __restrict__ x,
+                                                   const uint8_t* __restrict__ codes, int n_rows,
+                                                   int nblocks, int k_cols, int m_rows,
+                                                   float* __restrict__ y, float scale, Lut256 lut) {
+  mfma_sk8_body<ND, G, false>(x, codes, n_rows, nblocks, k_cols, m_rows, y, scale, lut);
+}
+
+template <int ND, int G>
+__global__ __launch_bounds__(1024) void k_mfma_sk8r(const uint16_t* __restrict__ x,
+                                                    const uint8_t* __restrict__ codes, int n_rows,
+                                                    int nblocks, int k_cols, int m_rows,
+                                                    float* __restrict__ y, float scale,
+                                                    Lut256 lut) {
+  mfma_sk8_body<ND, G, true>(x, codes, n_rows, nblocks, k_cols, m_rows, y, scale, lut);
 }
 
 // ------------------------------------------------------------------ device fit, exact Eq. 5
@@ -2966,6 +2991,22 @@ int32_t launch_mfma(const uint16_t* x, int M, int K, const LinearJob& j, hipStre
 // Split-K launch on 8-bit codes (one linear per launch).
 bool sk8_shape(int M, int K) { return M >= 2 && M <= 16 && (K == 2048 || K == 4096 || K == 8192); }
 
+// Split-K at any other K up to 8192 (k_mfma_sk8r), where it is the faster (MI355X, graph replay,
+// codes streamed from HBM; GEMV up to m = 8 unless m N > 65536, else stepped -> split-K): m = 3 from
+// N = 8192 (4096 x 7168 10.1 -> 11.3 us, 8192 x 3072 10.5 -> 8.7), m = 4, 5 from N = 4096
+// (m = 4: 2048 x 2560 5.7 -> 5.8, 4096 x 7168 12.0 -> 11.4), m = 6 .. 8 from N = 2048 (m = 6:
+// 1024 x 5120 7.2 -> 7.9, 2048 x 7168 11.2 -> 10.3; m = 8: 8192 x 7168 41.2 -> 18.1). Above m = 8 at
+// K <= 6144 everywhere to m = 12 (16383 x 5120 24.2 -> 23.0) and to N = 8192 above (m = 16: 4096 x
+// 3072 14.3 -> 8.8, 16383 x 5120 25.2 -> 25.4), at longer rows to N = 4096 and 2048 (m = 12: 4096 x
+// 7168 18.2 -> 17.9, 8192 x 7168 19.9 -> 24.9; m = 16: 2048 x 7168 17.7 -> 17.2, 4096 x 7168
+// 18.3 -> 19.2). From N = 16384 the stepped kernel has a workgroup for every other CU.
+bool sk8r_shape(int M, int64_t N, int K) {
+  if (M < 3 || M > 16 || N >= 16384 || K < 512 || K > 8192 || sk8_shape(M, K)) return false;
+  if (M <= 8) return N >= (M == 3 ? 8192 : M <= 5 ? 4096 : 2048);
+  if (K <= 6144) return M <= 12 || N <= 8192;
+  return N <= (M <= 12 ? 4096 : 2048);
+}
+
 int32_t launch_sk8(const uint16_t* x, int M, int K, const LinearJob& j, hipStream_t st, int cus) {
   Lut256 lut;
   float scale;
@@ -2976,6 +3017,19 @@ int32_t launch_sk8(const uint16_t* x, int M, int K, const LinearJob& j, hipStrea
 #define LOGBQ_SK8(ND, GG)                                                                        \
   hipLaunchKernelGGL((k_mfma_sk8<ND, GG>), dim3((unsigned)grid), dim3(1024), 0, st, x, j.codes, \
                      (int)j.n, nblocks, K, M, j.y, scale, lut)
+#define LOGBQ_SK8R(ND, GG)                                                                       \
+  hipLaunchKernelGGL((k_mfma_sk8r<ND, GG>), dim3((unsigned)grid), dim3(1024), 0, st, x, j.codes, \
+                     (int)j.n, nblocks, K, M, j.y, scale, lut)
+  if (!sk8_shape(M, K)) {
+    switch ((K + 2047) / 2048) {
+      case 1: if (g2) LOGBQ_SK8R(4, 2); else LOGBQ_SK8R(4, 1); break;
+      case 2: if (g2) LOGBQ_SK8R(8, 2); else LOGBQ_SK8R(8, 1); break;
+      case 3: if (g2) LOGBQ_SK8R(12, 2); else LOGBQ_SK8R(12, 1); break;
+      default: if (g2) LOGBQ_SK8R(16, 2); else LOGBQ_SK8R(16, 1); break;
+    }
+    return launch_status();
+  }
+#undef LOGBQ_SK8R
   switch (K) {
     case 2048: if (g2) LOGBQ_SK8(4, 2); else LOGBQ_SK8(4, 1); break;
     case 4096: if (g2) LOGBQ_SK8(8, 2); else LOGBQ_SK8(8, 1); break;
@@ -3301,6 +3355,7 @@ int choose_path(int M, int K, int64_t N, bool symmetric = true) {
       ((M >= 5 && M <= 8 && !(N <= 1024 && K >= 4096)) || (M <= 4 && M >= 3 && N >= 8192) ||
        (M >= 9 && !(K == 8192 && N > 16384))))
     return LOGBQ_PATH_SPLITK;
+  if (BITS == 8 && sk8r_shape(M, N, K)) return LOGBQ_PATH_SPLITK;
   if (sk_shape(M, K) && BITS == 4 &&
       ((M >= 5 && M <= 16) || (M == 4 && (N > 1024 || K <= 4096)) || (M == 3 && N >= 4096) ||
        (M > 16 && (K <= 4096 || N <= 16384 || M <= 20))))
@@ -3825,7 +3880,11 @@ int32_t logbq_linear_kernel(int32_t bits, int64_t m, int64_t k, int64_t n, const
     const int path = bits == 4 ? choose_path<4>(M, K, n, symmetric) : choose_path<8>(M, K, n);
     int wk = 0, cpl = 0;
     if (path == LOGBQ_PATH_SPLITK && bits == 8) {
-      std::snprintf(buf, sizeof(buf), "k_mfma_sk8<%d, %d>", K / 512, M <= 8 ? 2 : 1);
+      if (sk8_shape(M, K))
+        std::snprintf(buf, sizeof(buf), "k_mfma_sk8<%d, %d>", K / 512, M <= 8 ? 2 : 1);
+      else
+        std::snprintf(buf, sizeof(buf), "k_mfma_sk8r<%d, %d>", (K + 2047) / 2048 * 4,
+                      M <= 8 ? 2 : 1);
     } else if (path == LOGBQ_PATH_SPLITK && ((M <= 16 && K != 14336) || symmetric)) {
       const SkConfig c = sk_config(M, K, !symmetric, (int)((n + 15) / 16));
       if (!sk_shape(M, K))

@@ -162,3 +162,23 @@ def test_ragged_split_k(n, k):
                 assert torch.equal(a, b)
             else:
                 assert torch.equal(a, L.linear(x, c[:16], books[0]))
+
+
+@pytest.mark.parametrize("n,k", [(130, 512), (33, 1056), (2047, 2080), (2049, 4128), (4097, 6112),
+                                 (2048, 6176), (4096, 8160)])
+def test_ragged_split_k8(n, k):
+    """8-bit split-K at K outside its powers of two: one to four phases per wavefront, a last one
+    with 32 columns or all but 32, wavefronts with none, a partial last block of rows; two calls
+    bit-equal, within the float16 rounding of the codebook, 2^-11, plus k float32 sums."""
+    rng = np.random.default_rng([8, n, k])
+    c = torch.from_numpy(rng.integers(0, 256, size=(n, k), dtype=np.uint8)).to(DEV)
+    book = rng.standard_normal(256).astype(np.float32)
+    w = torch.tensor(book.astype(np.float64), device=DEV)[c.int()]
+    for m in (3, 4, 6, 8, 9, 12, 16):
+        print(f"ragged split-K 8 n={n} k={k} m={m} {L.linear_kernel(8, m, k, n)}", flush=True)
+        x = torch.from_numpy(rng.standard_normal((m, k)).astype(np.float16)).to(DEV)
+        y = torch.full((m, n), float("nan"), device=DEV)
+        L.linear8(x, c, book, out=y)
+        assert torch.equal(y, L.linear8(x, c, book))
+        bound = (x.double().abs() @ w.abs().T.contiguous()) * (2.0 ** -11 + k * 2.0 ** -24)
+        assert bool(((y.double() - x.double() @ w.T.contiguous()).abs() <= bound).all())
