@@ -864,7 +864,8 @@ __device__ __forceinline__ float row_lane(float v) {
 // One step of a slot: every lane's error of its own column (d: its U_ii and 1 / U_ii), lane L's
 // applied to the lanes after it and to the NS - 1 slots after this one (u: row 16 t + L of U at this
 // lane's column of each, 0 up to the diagonal). FAST lets the lanes up to L subtract that zero
-// times the error, which leaves every value but -0 as it is.
+// times the error, which leaves every value but -0 as it is (-0 becomes +0 where the error is
+// negative).
 template <int KIND, bool FAST, int NS, int L>
 __device__ __forceinline__ void gptq_step(float (&p)[8], float& a, float& e, int r,
                                           const float (&u)[NS], float2 d, const GptqQuant& qz) {
@@ -899,8 +900,10 @@ __device__ __forceinline__ void gptq_steps(float (&p)[8], float& a, float& e, in
 // Slot s: its steps are one dependent chain, so they run straight through on the forms that are
 // exact for ordinary values, with as many later slots as the block has left (rounded up to even).
 // If a value of the wavefront turns out not to be ordinary, the slot runs again from its start on
-// the general forms: a difference that is -0, tiny, huge or not finite, a value of -0, or an
-// extreme U_ii.
+// the general forms: a difference that is tiny, huge or not finite, an extreme U_ii, or a value
+// that enters the slot as -0. A difference of two values is -0 only if the first of them is, so a
+// value that is -0 at any of the slot's steps was -0 on entry; at the end of the steps its sign is
+// gone.
 template <int KIND>
 __device__ __forceinline__ float gptq_slot(float (&p)[8], int s, int r, const float* u, float2 d,
                                            const GptqQuant& qz) {
@@ -915,7 +918,7 @@ __device__ __forceinline__ float gptq_slot(float (&p)[8], int s, int r, const fl
   const float mag = __builtin_fabsf(a);
   const bool plain = (mag >= 8.673617379884035e-19f && mag < 1.152921504606847e18f) ||
                      __builtin_bit_cast(uint32_t, a) == 0u;   // 2^-60, 2^60
-  if (__any(d.y == 0.0f || !plain || __builtin_bit_cast(uint32_t, p[0]) == kMinusZero)) {
+  if (__any(d.y == 0.0f || !plain || __builtin_bit_cast(uint32_t, p0[0]) == kMinusZero)) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) p[q] = p0[q];
     gptq_steps<KIND, false, 8>(p, a, e, r, u, d, qz);

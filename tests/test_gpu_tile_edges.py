@@ -94,6 +94,56 @@ def test_gptq_edges(n, k, book, special):
     assert same.all(), f"{np.count_nonzero(~same)} of {same.size} weights differ"
 
 
+def _gptq_book(book, rng):
+    """Parameters of a codebook of each kind, and its quantizer for the oracle."""
+    fit_on = (0.02 * rng.standard_t(4, size=4096)).astype(np.float32)
+    p = L.fit_uniform(fit_on) if book == "uniform" else L.fit(fit_on)
+    if book == "any":
+        for i in range(1, 8):
+            p.codebook[8 + i] *= 1.125
+        p.codebook[0] = 0.001
+    levels, th = p.codebook_array(), np.ctypeslib.as_array(p.thresholds).copy()
+
+    def quantize(col):
+        if book == "uniform":
+            c = np.sum(col[:, None] >= th[None, :15], axis=1)
+        else:
+            c = np.sum(np.abs(col)[:, None] >= th[None, :7], axis=1)
+            c = np.where((col < 0) & (c > 0), c + 8, c)
+        return c.astype(np.uint8), levels[c]
+    return p, levels, quantize
+
+
+@pytest.mark.parametrize("book", ["mirrored", "any", "uniform"])
+@pytest.mark.parametrize("col", [0, 5, 37, 150])
+def test_gptq_minus_zero(book, col):
+    """A weight of -0 that no earlier error has moved is -0 when its column is quantized and is
+    returned as -0, whatever the errors of later columns; every other value is ordinary, so no
+    row takes the general form for another reason. Weights and the last block's errors bit for
+    bit against the CPU oracle's float32 loop."""
+    from oracle import gptq_oracle as G
+    n, k = 40, 160
+    print(f"gptq -0 {book} column {col}", flush=True)
+    rng, w, u = _gptq_case(n, k, [11, col])
+    p, levels, quantize = _gptq_book(book, rng)
+    # Every other row starts with values of the codebook, whose errors are +0, and keeps its -0;
+    # in the others a negative error times the zeros of U turns it to +0 (column 0: in none).
+    w[::2, :col] = levels[rng.integers(1, 8, (n // 2, col))]
+    w[:, col] = -0.0
+    u[:col, col] = 0.0
+    codes_ref, w_ref = G.gptq(w, u, quantize)
+    assert not w_ref[:, col].any() and np.signbit(w_ref[::2, col]).all()
+    wd = torch.from_numpy(w.copy()).to(DEV)
+    err = torch.full((n, L.GPTQ_BLOCK), float("nan"), device=DEV)
+    codes = L.gptq(wd, torch.from_numpy(u).to(DEV), p, workspace=err)
+    assert np.array_equal(codes.cpu().numpy(), codes_ref[:, 0::2] | (codes_ref[:, 1::2] << 4))
+    wrong = wd.cpu().numpy().view(np.uint32) != w_ref.view(np.uint32)
+    assert not wrong.any(), f"{np.count_nonzero(wrong)} weights differ"
+    last = (w_ref[:, 128:] - levels[codes_ref[:, 128:]]) / np.diag(u)[128:]
+    wrong = err[:, :32].cpu().numpy().view(np.uint32) != last.view(np.uint32)
+    assert not wrong.any(), f"{np.count_nonzero(wrong)} errors differ"
+
+
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("n,k,m", [(16640, 32, 257), (16385, 96, 320), (16383, 544, 513),
                                    (4097, 1056, 2049), (14336, 64, 1024), (4096, 14336, 1025),
