@@ -3108,13 +3108,12 @@ PfCfg pf_config(int M, int64_t N, int K, int bits) {
 // 410 -> 178; 8-bit 8199 x 3072 at m = 777: 173 -> 72, 14336 x 4096 at m = 2048: 698 -> 275).
 // Up to 256 rows the 4-bit K-quartered kernel keeps the layers that its grid covers in one round
 // (14336 x 4096 at m = 192: 44.8 us against 49.5; in two rounds 28672 x 2048: 55.1 -> 38.2, 28672 x
-// 8192: 167 -> 124), and the 8-bit one m = 129 .. 144, where its second row block stays in use and
-// under test (28672 x 8192 at m = 160: 263 -> 147).
+// 8192: 167 -> 124); 8-bit 28672 x 8192 at m = 129: 256 -> 136, at m = 160: 263 -> 147.
 // k < 2^22 and n < 2^21 keep the descriptors over 256 rows of codes, of activations and of y
 // below 2^31 bytes, m n < 2^36 the one-dimensional grid below 2^32 threads.
 bool pf_shape(int M, int64_t N, int K, int bits) {
   if (M <= 128 || K >= (1 << 22) || N >= (1 << 21) || M * N >= ((int64_t)1 << 36)) return false;
-  if (M <= 256 && (bits == 4 ? (N + 127) / 128 * 2 <= 256 : M <= 144)) return false;
+  if (bits == 4 && M <= 256 && (N + 127) / 128 * 2 <= 256) return false;
   const double stepped = step_config(M, N, K, bits, true).cost;
   return stepped < 0.0 || pf_config(M, N, K, bits).cost < stepped + 5.0;
 }

@@ -400,12 +400,12 @@ def test_fit_same_for_any_sort_thread_count(threads, monkeypatch):
 
 def test_prefill_path_rule():
     """Above m = 256 the prefill kernel runs unless the stepped kernel's launch shape fits on the
-    chip and is the cheaper one; from m = 129 (8-bit: 145) where the K-quartered kernel would need a
-    second round. Rows too long or layers too wide for its descriptors stay on the older kernels."""
+    chip and is the cheaper one; from m = 129 on 8-bit codes, and where the 4-bit K-quartered kernel
+    would need a second round. Rows too long or layers too wide for its descriptors stay on the older kernels."""
     lp, lk = L.linear_path, L.linear_kernel
     assert lp(4, 128, 4096, 28672) == "mfma_kq" and lp(4, 129, 4096, 28672) == "mfma_pf"
     assert lp(4, 256, 4096, 14336) == "mfma_kq" and lp(4, 257, 4096, 14336) == "mfma_pf"
-    assert lp(8, 144, 4096, 28672) == "mfma_kq" and lp(8, 145, 4096, 28672) == "mfma_pf"
+    assert lp(8, 128, 4096, 28672) == "mfma_kq" and lp(8, 129, 4096, 28672) == "mfma_pf"
     assert lk(4, 2048, 4096, 14336) == "k_mfma_pf<4, 4>" and lk(8, 777, 3072, 8199) == "k_mfma_pf<8, 2>"
     assert lp(4, 300, 4096, 1024) == "mfma" and lp(8, 512, 4096, 4096) == "mfma"
     assert lp(4, 300, 1 << 22, 28672) != "mfma_pf" and lp(4, 300, 4096, 1 << 21) != "mfma_pf"
