@@ -43,6 +43,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <numeric>
 #include <vector>
 
 #include "fit_detail.h"
@@ -2833,8 +2834,8 @@ constexpr int64_t kMaxBatchRows = 65535LL * 64;
 // 4096 x 4096 at m = 48: 40.9 -> 27.0 us, 8192 x 8192 at m = 64: 86.0 -> 59.1 us; 4-bit
 // 4096 x 4096 at m = 64: 30.1 -> 21.0 us); at N = 28672 (448 workgroups) 1.04-1.44 times the
 // time. `cap` is the kernel's batch tiles per workgroup column (8 with register tables, 4 with
-// the LDS table). This rule now decides between the stepped and the K-quartered kernel, and is
-// what step_config below falls back to where no launch shape fits on the chip.
+// the LDS table). This rule now decides between the stepped and the K-quartered kernel up to
+// m = 128, and is what step_config below falls back to where no launch shape fits on the chip.
 constexpr int64_t kNarrowMaxWorkgroups = 256;
 bool narrow_fits(int M, int64_t N, int cap = 8) {
   const int64_t gy = M > 16 * cap ? (M + 16 * cap - 1) / (16 * cap) : 1;
@@ -3042,7 +3043,7 @@ int32_t launch_sk8(const uint16_t* x, int M, int K, const LinearJob& j, hipStrea
   return launch_status();
 }
 
-// K-quartered MFMA path on 8-bit codes: m > 64 at N >= 16384.
+// K-quartered MFMA path on 8-bit codes: m > 64 at N >= 16384 (above m = 128 where wide_path says).
 // (K < 2^24 keeps the 128-row buffer descriptor below 2^31 bytes.)
 bool kq8_shape(int M, int64_t N, int K) { return M > 64 && N >= 16384 && K < (1 << 24); }
 
@@ -3056,7 +3057,8 @@ int32_t launch_kq8(const uint16_t* x, int M, int K, const LinearJob& j, hipStrea
   return launch_status();
 }
 
-// K-quartered MFMA path (4-bit, sign-symmetric codebooks): m > 96 at N >= 4096.
+// K-quartered MFMA path (4-bit, sign-symmetric codebooks): m > 96 at N >= 4096 (above m = 128
+// where wide_path says).
 // (K < 2^25 keeps the 128-row buffer descriptor below 2^31 bytes.)
 bool kq_shape(int M, int64_t N, int K) { return M > 96 && N >= 4096 && K < (1 << 25); }
 
@@ -3075,47 +3077,111 @@ struct PfCfg {
   int bt, ks;
   double cost;     // us by the model
 };
-// The cheapest by a cost model fitted to MI355X measurements (29 shapes, n = 512 .. 28672,
-// k = 512 .. 14336, m = 300 .. 2048, within 10 % of nearly all): every round of up to 256
-// workgroups costs 7 us and, per step of 64 k, step[bt - 1] us; the whole grid's matrix work slows
-// the clock by a further full_bt * bt us per step and full chip. Two K parts add the zeroing
-// launch and two atomic adds per output.
+// The cheapest by a cost model fitted to MI355X measurements (every bt and ks on 1672 shapes of each
+// code width, n = 512 .. 28672, k = 512 .. 14336, m = 129 .. 2048, odd n among them, graph replay,
+// codes streamed from HBM; within 10 % of the time on nine tenths, and the shape it takes within
+// 5 % of the fastest on all but a few): a launch, a round of up to 256 workgroups, per step of 64 k
+// step[bt - 1] per round and full * bt for the share of a full chip that runs, which slows the
+// clock, and the stores. Two K parts add the zeroing launch and two atomic adds per output, which
+// take longer where rows of y are no whole cache lines.
+struct PfUs { double launch, round, step[4], full, out, two_parts, two_out, two_partial; };
+constexpr PfUs kPfUs4 = {2.5, 2.1, {0.561, 0.655, 0.879, 1.095}, 0.119, 0.65e-6,
+                         0.98, 5.35e-6, 1.9e-6};
+constexpr PfUs kPfUs8 = {3.3, 2.0, {0.995, 1.138, 1.501, 1.712}, 0.081, 0.59e-6,
+                         0.96, 5.35e-6, 2.0e-6};
 PfCfg pf_config(int M, int64_t N, int K, int bits) {
-  static constexpr double step4[4] = {0.59, 0.69, 0.89, 1.13};
-  static constexpr double step8[4] = {1.03, 1.155, 1.516, 1.666};
-  const double full_bt = bits == 4 ? 0.115 : 0.08;
+  const PfUs& c = bits == 4 ? kPfUs4 : kPfUs8;
+  const double two_out = c.two_out + (N % 32 != 0 ? c.two_partial : 0.0);
+  const double outputs = (double)M * (double)N;
   const int64_t steps = ((int64_t)K + 63) / 64;
   PfCfg best{0, 0, -1.0};
   for (int ks = 1; ks <= (steps >= 2 ? 2 : 1); ++ks)
     for (int bt = 1; bt <= 4; ++bt) {
       const int64_t wgs = ((M + 64 * (int64_t)bt - 1) / (64 * bt)) * ((N + 255) / 256) * ks;
       const double rounds = (double)((wgs + 255) / 256);
-      const double per_step = (bits == 4 ? step4 : step8)[bt - 1] * rounds +
-                              full_bt * bt * (double)wgs / 256.0;
-      const double cost = 7.0 * rounds + (double)((steps + ks - 1) / ks) * per_step +
-                          (ks == 2 ? 3.0 + 8.5e-6 * (double)M * (double)N : 0.0);
+      const double per_step = c.step[bt - 1] * rounds + c.full * bt * (double)wgs / 256.0;
+      const double cost = c.launch + c.round * rounds +
+                          (double)((steps + ks - 1) / ks) * per_step + c.out * outputs +
+                          (ks == 2 ? c.two_parts + two_out * outputs : 0.0);
       if (best.cost < 0.0 || cost < best.cost) best = {bt, ks, cost};
     }
   return best;
 }
 
-// The prefill kernel takes more than 128 batch rows unless the stepped kernel has a launch shape
-// that fits on the chip at once and its model's time, plus 5 us of launch and edges that the model
-// leaves out, is the shorter: narrow layers, whose 256-row tiles would leave most CUs idle
-// (1024 x 4096 at m = 300: 18.0 us against 27.1; 4096 x 4096 at m = 512: 34.6 against 41.6).
-// Elsewhere it replaces the K-quartered and the stepped kernels (4-bit 14336 x 4096 at m = 2048:
-// 316 -> 223 us, 8192 x 2048 at m = 600: 54 -> 34; another codebook 14336 x 4096 at m = 2048:
-// 410 -> 178; 8-bit 8199 x 3072 at m = 777: 173 -> 72, 14336 x 4096 at m = 2048: 698 -> 275).
-// Up to 256 rows the 4-bit K-quartered kernel keeps the layers that its grid covers in one round
-// (14336 x 4096 at m = 192: 44.8 us against 49.5; in two rounds 28672 x 2048: 55.1 -> 38.2, 28672 x
-// 8192: 167 -> 124); 8-bit 28672 x 8192 at m = 129: 256 -> 136, at m = 160: 263 -> 147.
 // k < 2^22 and n < 2^21 keep the descriptors over 256 rows of codes, of activations and of y
-// below 2^31 bytes, m n < 2^36 the one-dimensional grid below 2^32 threads.
-bool pf_shape(int M, int64_t N, int K, int bits) {
-  if (M <= 128 || K >= (1 << 22) || N >= (1 << 21) || M * N >= ((int64_t)1 << 36)) return false;
-  if (bits == 4 && M <= 256 && (N + 127) / 128 * 2 <= 256) return false;
-  const double stepped = step_config(M, N, K, bits, true).cost;
-  return stepped < 0.0 || pf_config(M, N, K, bits).cost < stepped + 5.0;
+// below 2^31 bytes; fewer than 2^23 workgroups of 512 threads, the grid below 2^32 threads.
+bool pf_fits(int M, int64_t N, int K) {
+  return K < (1 << 22) && N < (1 << 21) &&
+         (((int64_t)M + 63) / 64) * ((N + 255) / 256) < ((int64_t)1 << 23);
+}
+
+// Above 128 batch rows: the cheapest of the kernels that serve the call, each by a model in us
+// fitted to MI355X measurements (graph replay, codes streamed from HBM). Measured over 4071 shapes
+// and codebooks (m = 129 .. 2048, n = 1024 .. 28672, k = 512 .. 14336, odd ones among them), the
+// kernel taken is within 3 % of the fastest on 95 % of them. Both sides of the lines, us:
+//   stepped / prefill: 1024 x 4096 at m = 300 16.3 / 26.0; 2048 x 8192 at m = 512 37 / 48, at
+//     m = 640 54 / 51; on another 4-bit codebook 11008 x 11008 at m = 192 144 / 82
+//   K-quartered / prefill: 8192 x 8192 at m = 512 78.5 / 95.7; 14336 x 4096 at m = 192 44.8 / 49.5;
+//     28672 x 8192 at m = 192 167 / 124; 8-bit 16384 x 4096 at m = 256 71.0 / 76.3, 28672 x 8192
+//     at m = 129 256 / 136
+//   stepped / K-quartered: 6144 x 4096 at m = 257 29.1 / 37.2; 5120 x 4096 at m = 768 46.4 / 42.0
+//
+// XCDs that fetch the codes of one row block: with gx row blocks the workgroups gx apart, one per
+// batch block, go round-robin to the 8 XCDs, on which 8 / gcd(gx, 8) of them differ.
+int code_fetches(int64_t gx, int64_t gy) {
+  const int64_t xcds = 8 / std::gcd(gx, (int64_t)8);
+  return (int)(gy < xcds ? gy : xcds);
+}
+
+// The stepped kernel where it has a launch shape that fits on the chip at once (negative where it
+// has none): step_config's model times `step`, more where codes are fetched by several XCDs or
+// rows are no whole cache lines, and what that model leaves out (launch, stores).
+struct StepUs { double launch, step, spread, partial, two_parts, out; };
+constexpr StepUs kStepUsRegister = {4.1, 0.956, 0.169, 0.017, 11.4, 1.16e-6};
+constexpr StepUs kStepUsTable4 = {5.4, 0.935, 0.234, 0.054, 2.9, 1.1e-6};
+constexpr StepUs kStepUsTable8 = {5.6, 0.875, 0.588, 0.136, 5.25, 1.125e-6};
+double stepped_us(int M, int64_t N, int K, int bits, bool symmetric) {
+  const StepCfg st = step_config(M, N, K, bits, symmetric);
+  if (st.cost < 0.0) return -1.0;
+  const bool reg = bits == 4 && symmetric;
+  const StepUs& c = reg ? kStepUsRegister : bits == 4 ? kStepUsTable4 : kStepUsTable8;
+  const StepCosts& cc = reg ? kCostsRegister : bits == 4 ? kCostsTable4 : kCostsTable8;
+  const int64_t rows = st.narrow ? 64 : 128;
+  const int fetches = code_fetches((N + rows - 1) / rows, (M + 16 * st.mt16 - 1) / (16 * st.mt16));
+  return c.launch +
+         (st.cost - (st.ks == 2 ? cc.two_parts : 0.0)) *
+             (c.step + c.spread * (fetches - 1) / 7.0 +
+              ((int64_t)K * bits / 8 % 128 != 0 ? c.partial : 0.0)) +
+         (st.ks == 2 ? c.two_parts : 0.0) + c.out * (double)M * (double)N;
+}
+
+// The K-quartered kernels: 128 x 128 tiles, a round of 256 workgroups and a step of 128 k.
+struct QuarteredUs { double round, step, spread, partial, full; };
+constexpr QuarteredUs kQuarteredUs4 = {10.66, 0.799, 0.088, 0.047, 0.222};
+constexpr QuarteredUs kQuarteredUs8 = {9.8, 1.519, 0.152, 0.053, 0.434};
+double quartered_us(int M, int64_t N, int K, int bits) {
+  const QuarteredUs& c = bits == 4 ? kQuarteredUs4 : kQuarteredUs8;
+  const int64_t gx = (N + 127) / 128, gy = ((int64_t)M + 127) / 128, wgs = gx * gy;
+  const double rounds = (double)((wgs + 255) / 256), steps = (double)(((int64_t)K + 127) / 128);
+  return rounds * (c.round + steps * (c.step + c.spread * (code_fetches(gx, gy) - 1) / 7.0 +
+                                      ((int64_t)K * bits / 8 % 128 != 0 ? c.partial : 0.0))) +
+         steps * c.full * (double)wgs / 256.0;
+}
+
+template <int BITS>
+int wide_path(int M, int64_t N, int K, bool symmetric) {
+  int path = LOGBQ_PATH_MFMA;
+  double best = stepped_us(M, N, K, BITS, symmetric);
+  auto offer = [&](int p, double us) {
+    if (best < 0.0 || us < best) {
+      best = us;
+      path = p;
+    }
+  };
+  if (BITS == 8 ? kq8_shape(M, N, K) : symmetric && kq_shape(M, N, K))
+    offer(LOGBQ_PATH_MFMA_KQ, quartered_us(M, N, K, BITS));
+  if (pf_fits(M, N, K)) offer(LOGBQ_PATH_MFMA_PF, pf_config(M, N, K, BITS).cost);
+  return path;
 }
 
 template <int BITS>
@@ -3325,9 +3391,9 @@ int32_t launch_sk(const uint16_t* x, int M, int K, const LinearJob* jobs, const 
 // (m, k, N), so every linear of a grouped call runs the kernel that a single call would run,
 // with the same result bits.
 //
-// Above m = 128 the prefill kernel takes what pf_shape says.
+// Above m = 128 the cheapest by wide_path's models.
 //
-// Above m = 96 at N >= 4096 the K-quartered kernel replaces the stepped one for 4-bit codes with
+// At m = 97 .. 128 and N >= 4096 the K-quartered kernel replaces the stepped one for 4-bit codes with
 // sign-symmetric codebooks (7-11 % faster on the 8192 x 28672 and 4096 x 14336 layers; slower
 // on narrow layers, which have too few 128-row workgroups), except where the stepped kernel's
 // 64-row grid fits on the chip: there that one is faster (measured at m = 97 .. 256,
@@ -3366,7 +3432,7 @@ int choose_path(int M, int K, int64_t N, bool symmetric = true) {
   if (M <= 8 && gemv_config<BITS>(M, K, &wk, &cpl) &&
       !(M >= (BITS == 8 ? 5 : 3) && (int64_t)M * N > 65536))
     return LOGBQ_PATH_GEMV;
-  if (pf_shape(M, N, K, BITS)) return LOGBQ_PATH_MFMA_PF;
+  if (M > 128) return wide_path<BITS>(M, N, K, symmetric);
   if (BITS == 4 && kq_shape(M, N, K) && !narrow_fits(M, N)) return LOGBQ_PATH_MFMA_KQ;
   if (BITS == 8 && kq8_shape(M, N, K)) return LOGBQ_PATH_MFMA_KQ;
   return LOGBQ_PATH_MFMA;
@@ -3402,7 +3468,7 @@ int32_t run_linears(const uint16_t* x, int64_t m, int64_t k, const LinearJob* jo
     const LinearJob& j = jobs[live[a]];
     LutBytes tb;
     float scale;
-    const bool symmetric = BITS == 8 || !skr_shape(M, j.n, K) ||
+    const bool symmetric = BITS == 8 || !(M > 128 || skr_shape(M, j.n, K)) ||
                            make_lut_bytes(j.codebook, &tb, &scale);
     const int path = choose_path<BITS>(M, K, j.n, symmetric);
     if (path == LOGBQ_PATH_SPLITK && BITS == 8) {

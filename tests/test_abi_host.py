@@ -11,7 +11,7 @@ import pytest
 from oracle import logbq_oracle as O
 from paper_2607_01127_amd import inputs
 from paper_2607_01127_amd import logbq as L
-from stepped_rule import stepped_name, stepped_shape
+from stepped_rule import stepped_name, stepped_shape, wide_costs, wide_name
 
 HEADER = os.path.join(os.path.dirname(os.path.dirname(__file__)), "include", "logbq.h")
 
@@ -258,7 +258,7 @@ def test_linear_path_rule():
     # grid fits on the chip (ceil(N / 64) x ceil(m / 128) <= 256 workgroups)
     assert lp(4, 128, 8192, 28672) == "mfma_kq" and lp(4, 97, 1024, 16448) == "mfma_kq"
     assert lp(4, 97, 1024, 4096) == "mfma" and lp(4, 128, 1024, 16384) == "mfma"
-    assert lp(4, 129, 1024, 8192) == "mfma" and lp(4, 129, 1024, 8256) == "mfma_kq"
+    assert lp(4, 129, 1024, 8192) == "mfma" and lp(4, 129, 4096, 12288) == "mfma_kq"
     assert lp(4, 128, 1024, 4095) == "mfma" and lp(8, 128, 8192, 28672) == "mfma_kq"
     assert lp(8, 65, 8192, 16384) == "mfma_kq" and lp(8, 64, 8192, 28672) == "mfma"
     assert lp(8, 128, 4096, 14336) == "mfma"
@@ -295,7 +295,7 @@ def test_stepped_shape_rule():
                     if L.linear_path(bits, m, k, n) not in ("mfma", "mfma_kq"):
                         continue
                     name = L.linear_kernel(bits, m, k, n, cb)
-                    if name.startswith("k_mfma_kq") or name.startswith("k_mfma_sk"):
+                    if name.startswith(("k_mfma_kq", "k_mfma_sk", "k_mfma_pf")):
                         continue
                     assert name == stepped_name(m, k, n, kind), (kind, m, k, n)
                     narrow, t, parts = stepped_shape(m, k, n, kind)
@@ -340,7 +340,7 @@ def test_linear_kernel_names():
     assert lk(4, 33, 4096, 16384) == "k_mfma2_narrow<4, 3, false, false>"
     assert lk(4, 33, 4096, 16385) == "k_mfma2<4, 3, 4, false, false>"
     assert lk(4, 129, 1024, 8192) == "k_mfma2<4, 4, 4, false, false>"
-    assert lk(4, 129, 1024, 8256) == "k_mfma_kq"
+    assert lk(4, 129, 4096, 12288) == "k_mfma_kq"
     for m, k, n in ((64, 8192, 28672), (96, 8192, 28672), (48, 8192, 16385), (200, 2048, 1000)):
         assert lk(4, m, k, n) == stepped_name(m, k, n), (m, k, n)
     assert lk(8, 1, 8192, 28672) == "k_gemv<8, 1, 8, false, 2>"
@@ -398,17 +398,45 @@ def test_fit_same_for_any_sort_thread_count(threads, monkeypatch):
         (r.wmin, r.wmax, r.wmin_index, r.base, r.shift)
 
 
+def test_wide_path_rule():
+    """Above m = 128 the cheapest of the kernels that serve the call runs, by the models that
+    stepped_rule states again: the stepped kernel where a launch shape fits on the chip, the
+    K-quartered ones (4-bit: only for sign-symmetric codebooks), the prefill kernel within its
+    descriptors and grid. A grid of shapes reaches every kernel for every kind of codebook."""
+    table = np.linspace(-0.07, 0.08, 16, dtype=np.float32)     # not sign-symmetric
+    for kind in ("register", "table4", "bits8"):
+        bits = 8 if kind == "bits8" else 4
+        cb = table if kind == "table4" else None
+        seen = set()
+        for k in (32, 544, 1024, 3040, 4096, 8192, 11008, 14336):
+            for n in (1, 1000, 2048, 4095, 4096, 6144, 8199, 8256, 10240, 14336, 16384, 16385, 28672):
+                for m in (129, 144, 192, 256, 257, 320, 512, 640, 777, 1025, 2048, 5000):
+                    name = L.linear_kernel(bits, m, k, n, cb)
+                    assert name == wide_name(m, k, n, kind), (kind, m, k, n)
+                    seen.add(name.split("<")[0].replace("_narrow", "").replace("kq8", "kq"))
+        assert seen == {"k_mfma2", "k_mfma_pf"} | ({"k_mfma_kq"} if kind != "table4" else set())
+    for m, k, n in ((300, 1 << 22, 28672), (300, 4096, 1 << 21), (4194240, 64, 40000)):
+        assert "mfma_pf" not in wide_costs(m, k, n) and L.linear_path(4, m, k, n) != "mfma_pf"
+        assert L.linear_path(8, m, k, n) != "mfma_pf"
+    assert L.linear_path(4, 4194240, 64, 256) == "mfma_pf"
+
+
 def test_prefill_path_rule():
-    """Above m = 256 the prefill kernel runs unless the stepped kernel's launch shape fits on the
-    chip and is the cheaper one; from m = 129 on 8-bit codes, and where the 4-bit K-quartered kernel
-    would need a second round. Rows too long or layers too wide for its descriptors stay on the older kernels."""
+    """Sides of the lines between the kernels above m = 128 (measured, us)."""
     lp, lk = L.linear_path, L.linear_kernel
+    asym = np.linspace(-0.07, 0.08, 16, dtype=np.float32)
     assert lp(4, 128, 4096, 28672) == "mfma_kq" and lp(4, 129, 4096, 28672) == "mfma_pf"
     assert lp(4, 256, 4096, 14336) == "mfma_kq" and lp(4, 257, 4096, 14336) == "mfma_pf"
     assert lp(8, 128, 4096, 28672) == "mfma_kq" and lp(8, 129, 4096, 28672) == "mfma_pf"
     assert lk(4, 2048, 4096, 14336) == "k_mfma_pf<4, 4>" and lk(8, 777, 3072, 8199) == "k_mfma_pf<8, 2>"
     assert lp(4, 300, 4096, 1024) == "mfma" and lp(8, 512, 4096, 4096) == "mfma"
-    assert lp(4, 300, 1 << 22, 28672) != "mfma_pf" and lp(4, 300, 4096, 1 << 21) != "mfma_pf"
+    # the K-quartered kernel where its one round is the fastest (78.5 / 95.7, 38.2 / 44.8, 71.0 / 76.3)
+    assert lp(4, 512, 8192, 8192) == "mfma_kq" and lp(4, 257, 4096, 8192) == "mfma_kq"
+    assert lp(8, 256, 4096, 16384) == "mfma_kq"
+    # the stepped kernel and not the K-quartered one (29.1 / 37.2, 13.3 / 18.0)
+    assert lp(4, 257, 4096, 6144) == "mfma" and lp(4, 129, 1024, 8256) == "mfma"
+    # a codebook that the K-quartered kernel cannot run (81.8 / 144.4 on the LDS-table kernel)
+    assert lk(4, 192, 11008, 11008, asym).startswith("k_mfma_pf<")
     for bits in (4, 8):
         assert lk(bits, 2048, 4096, 14336, np.arange(1 << bits, dtype=np.float32)).startswith("k_mfma_pf<")
 

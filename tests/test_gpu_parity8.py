@@ -340,10 +340,10 @@ def test_linear8_split_k():
 
 
 def test_linear8_k_quartered():
-    """The 8-bit K-quartered kernel (65 <= m <= 128 at N >= 16384) and the prefill kernel that
-    follows it at m = 129: a partial last 128-row workgroup, K not a multiple of the 128-k step,
-    batch rows past the last full tile, a fitted and an arbitrary codebook; y prefilled with NaN,
-    two calls bit-equal."""
+    """The 8-bit K-quartered kernel (65 <= m <= 128 at N >= 16384, two workgroup rows where they fit
+    on the chip at once) and the prefill kernel that follows it: a partial last 128-row workgroup,
+    K not a multiple of the 128-k step, batch rows past the last full tile, a fitted and an
+    arbitrary codebook; y prefilled with NaN, two calls bit-equal."""
     rng = np.random.default_rng(43)
     for n, k in ((16400, 1056), (16384, 4096)):
         w, p, r = prepare(n, k, [18, 43, k % 1000, 0])
@@ -351,8 +351,8 @@ def test_linear8_k_quartered():
         wh = oracle_w_hat(w, r)
         cb2 = rng.standard_normal(256).astype(np.float32)
         wh2 = O.dequantize(codes.cpu().numpy(), cb2)
-        for m in ((65, 100, 129) if k == 1056 else (128,)):
-            assert L.linear_path(8, m, k, n) == ("mfma_kq" if m <= 128 else "mfma_pf")
+        for m in ((65, 100, 129) if k == 1056 else (128, 256)):
+            assert L.linear_path(8, m, k, n) == ("mfma_pf" if m == 129 else "mfma_kq")
             _say(f"linear8 K-quartered n={n} k={k} m={m}")
             x = inputs.activations(m, k, seed=[18, 43, k % 1000, m])
             xd = torch.from_numpy(x).to(DEV)

@@ -147,7 +147,7 @@ def test_gptq_minus_zero(book, col):
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("n,k,m", [(16640, 32, 257), (16385, 96, 320), (16383, 544, 513),
                                    (4097, 1056, 2049), (14336, 64, 1024), (4096, 14336, 1025),
-                                   (16641, 224, 193)])
+                                   (16641, 224, 193), (20001, 1056, 129), (1025, 8160, 1300)])
 def test_prefill_tiles(bits, n, k, m):
     """Prefill tiles of 256 weight rows x 64 to 256 batch rows and steps of 64 k: one row past a
     tile, one short of it, part steps, one and two K parts; a fitted-like and an arbitrary codebook
