@@ -2995,20 +2995,26 @@ int32_t launch_mfma(const uint16_t* x, int M, int K, const LinearJob& j, hipStre
 // Split-K launch on 8-bit codes (one linear per launch).
 bool sk8_shape(int M, int K) { return M >= 2 && M <= 16 && (K == 2048 || K == 4096 || K == 8192); }
 
-// Split-K at any other K up to 8192 (k_mfma_sk8r), where it is the faster (MI355X, graph replay,
-// codes streamed from HBM; GEMV up to m = 8 unless m N > 65536, else stepped -> split-K): m = 3 from
-// N = 8192 (4096 x 7168 10.1 -> 11.3 us, 8192 x 3072 10.5 -> 8.7), m = 4, 5 from N = 4096
-// (m = 4: 2048 x 2560 5.7 -> 5.8, 4096 x 7168 12.0 -> 11.4), m = 6 .. 8 from N = 2048 (m = 6:
-// 1024 x 5120 7.2 -> 7.9, 2048 x 7168 11.2 -> 10.3; m = 8: 8192 x 7168 41.2 -> 18.1). Above m = 8 at
-// K <= 6144 everywhere to m = 12 (16383 x 5120 24.2 -> 23.0) and to N = 8192 above (m = 16: 4096 x
-// 3072 14.3 -> 8.8, 16383 x 5120 25.2 -> 25.4), at longer rows to N = 4096 and 2048 (m = 12: 4096 x
-// 7168 18.2 -> 17.9, 8192 x 7168 19.9 -> 24.9; m = 16: 2048 x 7168 17.7 -> 17.2, 4096 x 7168
-// 18.3 -> 19.2). From N = 16384 the stepped kernel has a workgroup for every other CU.
+// Split-K at any other K up to 8192 (k_mfma_sk8r), where it is the faster. MI355X, graph replay,
+// codes streamed from HBM, split-K's time over the other kernel's:
+// m = 3 .. 8 against the GEMV (m <= 4, or m N <= 65536): m = 3 from N = 8192 (0.75 .. 1.0; 4096 x
+//   7168 1.12), m = 4, 5 from N = 4096, m = 6 .. 8 from N = 2048 (0.42 .. 1.0; 1024 x 7168 1.2 ..
+//   1.4). At m = 3, 4 not below K = 1024 (1.0 .. 1.14), nor at K in the last 128 below 4096 and 8192,
+//   where every lane of the GEMV has a chunk (8192 x 8160 at m = 3 25.4 against 16.7 us; 4064 1.09);
+//   at m = 6 .. 8 those below 8192 from N = 4096 (2048 x 8160 at m = 6 1.10).
+// m = 5 .. 8 against the stepped kernel: from K = 1024 (12288 x 1056 0.79, 16383 x 640 1.11).
+// m = 9 .. 16 (stepped): below K = 1024 to N = 8192 (8192 x 640 0.87, 12288 x 512 at m = 12 1.20); to
+//   K = 6144 everywhere up to m = 12 (0.5 .. 1.09) and to N = 8192 above (16383 x 5120 at m = 16
+//   1.17); longer rows to N = 4096 up to m = 12 (0.92 .. 0.99; K > 8064 1.01 .. 1.14: to N = 2048)
+//   and to N = 2048 above (4096 x 7680 1.05).
 bool sk8r_shape(int M, int64_t N, int K) {
   if (M < 3 || M > 16 || N >= 16384 || K < 512 || K > 8192 || sk8_shape(M, K)) return false;
-  if (M <= 8) return N >= (M == 3 ? 8192 : M <= 5 ? 4096 : 2048);
+  if (M <= 4) return N >= (M == 3 ? 8192 : 4096) && K >= 1024 && K % 4096 <= 3968;
+  if (M <= 8)
+    return M * N <= 65536 ? N >= (M == 5 || K > 8064 ? 4096 : 2048) : K >= 1024;
+  if (K < 1024) return N <= 8192;
   if (K <= 6144) return M <= 12 || N <= 8192;
-  return N <= (M <= 12 ? 4096 : 2048);
+  return N <= (M <= 12 && K <= 8064 ? 4096 : 2048);
 }
 
 int32_t launch_sk8(const uint16_t* x, int M, int K, const LinearJob& j, hipStream_t st, int cus) {
@@ -3219,18 +3225,22 @@ bool sk_shape(int M, int K) {
 }
 
 // Split-K at any other K (k_mfma_skr): 4-bit codes of sign-symmetric codebooks (any other codebook
-// takes the kernel that the remaining rules name), 512 <= K <= 16384. Where it is the faster
-// (MI355X, graph replay, codes streamed from HBM; GEMV up to m = 8, stepped kernel above -> split-K):
-// m = 3 from N = 4096 (1024 x 5120 4.6 -> 6.0 us, 4096 x 5120 7.4 -> 6.4, 13824 x 5120 17.6 -> 12.2);
-// m = 4, 5 above N = 1024 (1024 x 11008 at m = 5 7.9 -> 8.4, 2048 x 2560 5.4 -> 4.7, 4096 x 11008
-// 18.8 -> 10.9); m = 6 .. 8 everywhere (1024 x 3072 at m = 8 6.8 -> 5.1, 4096 x 11008 26.9 -> 11.2,
-// 8192 x 7168 29.6 -> 12.1); above m = 8 up to N = 8192 at K <= 4096 (m = 16: 8192 x 3072
-// 10.0 -> 9.3, 16000 x 3072 10.8 -> 12.3), else up to N = 4096 (m = 12: 4096 x 11008 17.2 -> 14.9,
-// 8192 x 7168 13.8 -> 15.1) and above m = 12 up to N = 2048 (m = 16: 2048 x 7168 12.5 -> 11.5,
-// 4096 x 11008 17.3 -> 17.9). From N = 16384 the stepped kernel has a workgroup for every other CU.
+// takes the kernel that the remaining rules name), 512 <= K <= 16384, where it is the faster.
+// MI355X, graph replay, codes streamed from HBM, split-K's time over the other kernel's:
+// m = 3 .. 8 against the GEMV (m N <= 65536): m = 3 from N = 4096 (0.64 .. 0.96; 2048 x 7136 1.08),
+//   m = 4, 5 above N = 1024 (0.38 .. 0.98; 1024 x 13856 1.15), m = 6 .. 8 everywhere (0.31 .. 0.95).
+// m = 5 .. 8 against the stepped kernel: from K = 2048 (0.69 .. 1.02), to N = 12288 from K = 896
+//   (12288 x 896 0.95, x 768 1.08; 16383 x 1536 1.09).
+// m = 9 .. 16 (stepped) up to N = 8192 at K <= 4096 (0.65 .. 0.97; 12288 x 3040 at m = 13 0.93, 14336 x
+//   2080 1.09), else up to N = 4096 (m = 12 0.62 .. 0.95; 6144 x 9216 1.04) and above m = 12 up to
+//   N = 2048 (m = 16: 2048 x 7168 0.87, 4096 x 11008 1.01). From N = 16384 the stepped kernel has a
+//   workgroup for every other CU.
 bool skr_shape(int M, int64_t N, int K) {
   if (M < 3 || M > 16 || N >= 16384 || K < 512 || K > 16384 || sk_shape(M, K)) return false;
-  if (M <= 8) return M >= 6 || (M >= 4 ? N > 1024 : N >= 4096);
+  if (M <= 8) {
+    if (M * N <= 65536) return M >= 6 || (M >= 4 ? N > 1024 : N >= 4096);
+    return K >= (N <= 12288 ? 896 : 2048);
+  }
   return N <= (K <= 4096 ? 8192 : M <= 12 ? 4096 : 2048);
 }
 

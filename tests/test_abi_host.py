@@ -452,8 +452,19 @@ def test_ragged_split_k_rule():
     assert lp(4, 17, 11008, 4096) == "mfma" and lp(4, 8, 3072, 16384) == "mfma"
     assert lp(4, 9, 16416, 1024) == "mfma" and lp(4, 8, 480, 64) == "gemv"
     assert lk(4, 8, 11008, 4096, np.arange(16, dtype=np.float32)) == "k_gemv<4, 8, 1, true, 2>"
+    # short rows where the stepped kernel is the other one (m N > 65536), GEMV below
+    assert lp(4, 8, 544, 8192) == "splitk" and lp(4, 8, 544, 8193) == "mfma"
+    assert lp(4, 8, 896, 12288) == "splitk" and lp(4, 8, 864, 12288) == "mfma"
+    assert lp(4, 5, 2016, 14336) == "mfma" and lp(4, 5, 2080, 14336) == "splitk"
     # 8-bit codes up to K = 8192
     assert lk(8, 8, 5120, 4096) == "k_mfma_sk8r<12, 2>" and lk(8, 9, 544, 64) == "k_mfma_sk8r<4, 1>"
     assert lp(8, 3, 3072, 8191) == "gemv" and lp(8, 3, 3072, 8192) == "splitk"
     assert lp(8, 12, 7168, 4096) == "splitk" and lp(8, 13, 7168, 4096) == "mfma"
+    assert lp(8, 3, 992, 8192) == "gemv" and lp(8, 4, 1056, 4096) == "splitk"
+    assert lp(8, 3, 3968, 8192) == "splitk" and lp(8, 3, 4064, 8192) == "gemv"
+    assert lp(8, 4, 8064, 8192) == "splitk" and lp(8, 4, 8160, 8192) == "gemv"
+    assert lp(8, 6, 8160, 4095) == "gemv" and lp(8, 6, 8160, 4096) == "splitk"
+    assert lp(8, 5, 992, 14336) == "mfma" and lp(8, 5, 1056, 14336) == "splitk"
+    assert lp(8, 9, 992, 8192) == "splitk" and lp(8, 9, 992, 8193) == "mfma"
+    assert lp(8, 12, 8064, 4096) == "splitk" and lp(8, 12, 8160, 4096) == "mfma"
     assert lp(8, 9, 8224, 1024) == "mfma" and lp(8, 8, 3072, 16384) == "mfma"
