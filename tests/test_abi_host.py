@@ -442,14 +442,14 @@ def test_prefill_path_rule():
 
 
 def test_ragged_split_k_rule():
-    """Split-K outside its powers of two: fitted 4-bit codebooks, 3 <= m <= 16, n < 16384; another
+    """Split-K outside its powers of two: fitted 4-bit codebooks, 3 <= m <= 16; another
     codebook takes the kernel that the remaining rules name."""
     lp, lk = L.linear_path, L.linear_kernel
     assert lp(4, 8, 11008, 4096) == "splitk" and lk(4, 8, 11008, 4096) == "k_mfma_skr<16, 2, 2>"
     assert lk(4, 16, 3072, 1000) == "k_mfma_skr<8, 1, 1>" and lk(4, 6, 544, 64) == "k_mfma_skr<4, 2, 1>"
     assert lk(4, 4, 5120, 2048) == "k_mfma_skr<8, 2, 2>" and lk(4, 4, 5120, 2049) == "k_mfma_skr<16, 2, 1>"
     assert lp(4, 2, 11008, 4096) == "gemv" and lp(4, 3, 11008, 4095) == "gemv"
-    assert lp(4, 17, 11008, 4096) == "mfma" and lp(4, 8, 3072, 16384) == "mfma"
+    assert lp(4, 17, 11008, 4096) == "mfma" and lp(4, 8, 3072, 16384) == "splitk"
     assert lp(4, 9, 16416, 1024) == "mfma" and lp(4, 8, 480, 64) == "gemv"
     assert lk(4, 8, 11008, 4096, np.arange(16, dtype=np.float32)) == "k_gemv<4, 8, 1, true, 2>"
     # short rows where the stepped kernel is the other one (m N > 65536), GEMV below
@@ -463,8 +463,19 @@ def test_ragged_split_k_rule():
     assert lp(8, 3, 992, 8192) == "gemv" and lp(8, 4, 1056, 4096) == "splitk"
     assert lp(8, 3, 3968, 8192) == "splitk" and lp(8, 3, 4064, 8192) == "gemv"
     assert lp(8, 4, 8064, 8192) == "splitk" and lp(8, 4, 8160, 8192) == "gemv"
-    assert lp(8, 6, 8160, 4095) == "gemv" and lp(8, 6, 8160, 4096) == "splitk"
+    assert lp(8, 6, 8160, 2559) == "gemv" and lp(8, 6, 8160, 2560) == "splitk"
+    assert lp(8, 6, 8064, 2048) == "splitk" and lp(8, 8, 8160, 2048) == "splitk"
     assert lp(8, 5, 992, 14336) == "mfma" and lp(8, 5, 1056, 14336) == "splitk"
     assert lp(8, 9, 992, 8192) == "splitk" and lp(8, 9, 992, 8193) == "mfma"
     assert lp(8, 12, 8064, 4096) == "splitk" and lp(8, 12, 8160, 4096) == "mfma"
-    assert lp(8, 9, 8224, 1024) == "mfma" and lp(8, 8, 3072, 16384) == "mfma"
+    assert lp(8, 9, 8224, 1024) == "mfma" and lp(8, 8, 3072, 16384) == "splitk"
+    # wide layers: the GEMV never, the stepped kernel where its last round is (nearly) full
+    for bits in (4, 8):
+        assert lp(bits, 3, 5120, 21845) == "splitk" and lp(bits, 4, 5120, 16384) == "splitk"
+        for m in (5, 8):
+            assert lp(bits, m, 5120, 24576) == "splitk" and lp(bits, m, 5120, 24577) == "mfma"
+            assert lp(bits, m, 5120, 32768) == "mfma" and lp(bits, m, 5120, 32769) == "splitk"
+            assert lp(bits, m, 5120, 49152) == "splitk" and lp(bits, m, 5120, 49153) == "mfma"
+    assert lp(4, 4, 2016, 20480) == "mfma" and lp(8, 4, 5120, 128256) == "splitk"
+    assert lp(8, 12, 5120, 20480) == "splitk" and lp(8, 13, 5120, 20480) == "mfma"
+    assert lp(8, 9, 2560, 16383) == "splitk" and lp(8, 9, 2560, 16384) == "mfma"

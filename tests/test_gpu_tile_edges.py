@@ -181,7 +181,8 @@ def test_prefill_tiles(bits, n, k, m):
 
 
 @pytest.mark.parametrize("n,k", [(130, 512), (33, 1056), (40, 4128), (4097, 4064), (2047, 8160),
-                                 (2049, 8224), (1025, 11008), (4099, 16352)])
+                                 (2049, 8224), (1025, 11008), (4099, 16352), (16399, 2080),
+                                 (32785, 2080)])
 def test_ragged_split_k(n, k):
     """Split-K at K outside its powers of two: a last wavefront with one column block of 32 or all
     but one, one and two K parts, a partial last block of rows. Single calls repeat their bits, a
@@ -215,7 +216,7 @@ def test_ragged_split_k(n, k):
 
 
 @pytest.mark.parametrize("n,k", [(130, 512), (33, 1056), (2047, 2080), (2049, 4128), (4097, 6112),
-                                 (2048, 6176), (4096, 8160)])
+                                 (2048, 6176), (4096, 8160), (16399, 1056), (32785, 2080)])
 def test_ragged_split_k8(n, k):
     """8-bit split-K at K outside its powers of two: one to four phases per wavefront, a last one
     with 32 columns or all but 32, wavefronts with none, a partial last block of rows; two calls
