@@ -3007,17 +3007,18 @@ bool ragged_width(int64_t N) { return N <= 24576 || (N > 32768 && (N - 1) % 3276
 // Split-K at any other K up to 8192 (k_mfma_sk8r), where it is the faster. MI355X, graph replay,
 // codes streamed from HBM, split-K's time over the other kernel's:
 // m = 3 .. 8 against the GEMV (m <= 4, or m N <= 65536): m = 3 from N = 8192 (0.49 .. 1.0; 4096 x
-//   7168 1.12; at any width, 57344 x 5120 0.52), m = 4, 5 from N = 4096, m = 6 .. 8 from N = 2048 (0.42 .. 1.0; 1024 x 7168 1.2 ..
-//   1.4). At m = 3, 4 not below K = 1024 (1.0 .. 1.14), nor at K in the last 128 below 4096 and 8192,
-//   where every lane of the GEMV has a chunk (8192 x 8160 at m = 3 25.4 against 16.7 us; 4064 1.09);
-//   at m = 6, 7 those below 8192 from N = 2560 (at m = 6 2048 x 8160 1.10, 2981 x 8160 0.94).
+//   7168 1.12; at any width, 57344 x 5120 0.52), m = 4, 5 from N = 4096, m = 6 .. 8 from N = 2048
+//   (0.42 .. 1.0; 1024 x 7168 1.2 .. 1.4). At m = 3, 4 not below K = 1024 (1.0 .. 1.14), nor at K in
+//   the last 128 below 4096 and 8192, where every lane of the GEMV has a chunk (8192 x 8160 at m = 3
+//   25.4 against 16.7 us; 4064 1.09); at m = 6, 7 those below 8192 from N = 2560 (at m = 6 2048 x 8160
+//   1.10, 2981 x 8160 0.94).
 // m = 5 .. 8 against the stepped kernel: from K = 1024 (12288 x 1056 0.79, 16383 x 640 1.11) on the
 //   widths above.
 // m = 9 .. 16 (stepped): below K = 1024 to N = 8192 (8192 x 640 0.87, 12288 x 512 at m = 12 1.20); to
 //   K = 6144 on the widths above up to m = 12 (0.5 .. 1.09; 20480 x 5120 0.82; not 16384 rows, with
-//   which 256 stepped workgroups of 64 rows fill the chip: 16384 x 2560 1.08) and to N = 8192 above (16383 x 5120 at m = 16
-//   1.17); longer rows to N = 4096 up to m = 12 (0.92 .. 0.99; K > 8064 1.01 .. 1.14: to N = 2048)
-//   and to N = 2048 above (4096 x 7680 1.05).
+//   which 256 stepped workgroups of 64 rows fill the chip: 16384 x 2560 1.08) and to N = 8192 above
+//   (16383 x 5120 at m = 16 1.17); longer rows to N = 4096 up to m = 12 (0.92 .. 0.99; K > 8064 1.01 ..
+//   1.14: to N = 2048) and to N = 2048 above (4096 x 7680 1.05).
 bool sk8r_shape(int M, int64_t N, int K) {
   if (M < 3 || M > 16 || K < 512 || K > 8192 || sk8_shape(M, K)) return false;
   if (M <= 4) return N >= (M == 3 ? 8192 : 4096) && K >= 1024 && K % 4096 <= 3968;
@@ -3244,15 +3245,20 @@ bool sk_shape(int M, int K) {
 // m = 3 .. 8 against the stepped kernel: from K = 2048 (0.58 .. 1.02) on the widths that
 //   ragged_width names, to N = 12288 from K = 896 (12288 x 896 0.95, x 768 1.08; 16383 x 1536 1.09).
 // m = 9 .. 16 (stepped) up to N = 8192 at K <= 4096 (0.65 .. 0.97; 12288 x 3040 at m = 13 0.93, 14336 x
-//   2080 1.09), else up to N = 4096 (m = 12 0.62 .. 0.95; 6144 x 9216 1.04) and above m = 12 up to
-//   N = 2048 (m = 16: 2048 x 7168 0.87, 4096 x 11008 1.01).
+//   2080 1.09); longer rows up to N = 4096 to m = 14 (0.62 .. 0.99; 6144 x 9216 at m = 12 1.04) and to
+//   N = 2048 above (m = 16: 2048 x 7168 0.87, 4096 x 11008 1.01). Up to m = 12 also to N = 6144 from
+//   K = 12288 (m = 12: 6144 x 12288 0.97, x 16352 0.88; 8192 x 13824 1.09), and above K = 5120 to
+//   N = 12288 where the stepped kernel has too many workgroups for two K parts, from 8193 rows on
+//   (0.79 .. 1.04; m = 9: 10240 x 11008 0.87, 12288 x 12288 0.86, 14336 x 9216 1.00).
 bool skr_shape(int M, int64_t N, int K) {
   if (M < 3 || M > 16 || K < 512 || K > 16384 || sk_shape(M, K)) return false;
   if (M <= 8) {
     if (M * N <= 65536) return M >= 6 || (M >= 4 ? N > 1024 : N >= 4096);
     return K >= (N <= 12288 ? 896 : 2048) && ragged_width(N);
   }
-  return N <= (K <= 4096 ? 8192 : M <= 12 ? 4096 : 2048);
+  if (K <= 4096) return N <= 8192;
+  return N <= (M <= 12 && K >= 12288 ? 6144 : M <= 14 ? 4096 : 2048) ||
+         (M <= 12 && K > 5120 && N > 8192 && N <= 12288);
 }
 
 // Split-K configuration: code dwords per lane and row, wavefronts per workgroup, batch groups,

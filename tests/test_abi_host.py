@@ -452,6 +452,12 @@ def test_ragged_split_k_rule():
     assert lp(4, 17, 11008, 4096) == "mfma" and lp(4, 8, 3072, 16384) == "splitk"
     assert lp(4, 9, 16416, 1024) == "mfma" and lp(4, 8, 480, 64) == "gemv"
     assert lk(4, 8, 11008, 4096, np.arange(16, dtype=np.float32)) == "k_gemv<4, 8, 1, true, 2>"
+    # m > 8: longer rows on more layers
+    assert lp(4, 12, 11008, 4096) == "splitk" and lp(4, 12, 11008, 4097) == "mfma"
+    assert lp(4, 12, 12288, 6144) == "splitk" and lp(4, 12, 12288, 6145) == "mfma"
+    assert lp(4, 9, 5152, 8192) == "mfma" and lp(4, 9, 5152, 8193) == "splitk"
+    assert lp(4, 12, 12288, 12288) == "splitk" and lp(4, 12, 12288, 12289) == "mfma"
+    assert lp(4, 14, 16384, 4096) == "splitk" and lp(4, 15, 16384, 4096) == "mfma"
     # short rows where the stepped kernel is the other one (m N > 65536), GEMV below
     assert lp(4, 8, 544, 8192) == "splitk" and lp(4, 8, 544, 8193) == "mfma"
     assert lp(4, 8, 896, 12288) == "splitk" and lp(4, 8, 864, 12288) == "mfma"
