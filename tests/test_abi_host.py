@@ -371,8 +371,9 @@ def test_linear_kernel_names():
 @pytest.mark.parametrize("scale", [1e-35, 1e30])
 def test_fit8_extreme_shift_thresholds(scale):
     """An 8-bit codebook (b near 1) on weights far from 1 has a shift s in the thousands; its
-    exact thresholds need b^n for n near 2 s. They equal the oracle's and take well under a
-    second (the fit builds each power once by squaring)."""
+    thresholds are decided by intervals around b^n for n near 2 s. They equal the oracle's and take
+    well under a second. (The exact integers that decide what an interval leaves open: see
+    test_fit_thresholds.)"""
     import time
     w = (np.random.default_rng(3).standard_t(3, 4000) * scale).astype(np.float32)
     t0 = time.perf_counter()
