@@ -474,6 +474,9 @@ def test_ragged_split_k_rule():
     assert lp(8, 6, 8064, 2048) == "splitk" and lp(8, 8, 8160, 2048) == "splitk"
     assert lp(8, 5, 992, 14336) == "mfma" and lp(8, 5, 1056, 14336) == "splitk"
     assert lp(8, 9, 992, 8192) == "splitk" and lp(8, 9, 992, 8193) == "mfma"
+    assert lp(8, 9, 608, 4096) == "splitk" and lp(8, 9, 608, 4097) == "mfma"
+    assert lp(8, 13, 4064, 8192) == "splitk" and lp(8, 13, 4128, 8192) == "mfma"
+    assert lp(8, 16, 6144, 4096) == "splitk" and lp(8, 12, 6144, 8192) == "splitk"
     assert lp(8, 12, 8064, 4096) == "splitk" and lp(8, 12, 8160, 4096) == "mfma"
     assert lp(8, 9, 8224, 1024) == "mfma" and lp(8, 8, 3072, 16384) == "splitk"
     # wide layers: the GEMV never, the stepped kernel where its last round is (nearly) full
