@@ -3015,12 +3015,11 @@ bool ragged_width(int64_t N) { return N <= 24576 || (N > 32768 && (N - 1) % 3276
 // m = 5 .. 8 against the stepped kernel: from K = 1024 (12288 x 1056 0.79, 16383 x 640 1.11) on the
 //   widths above.
 // m = 9 .. 16 (stepped): below K = 1024 to N = 8192 (8192 x 640 0.87, 12288 x 512 at m = 12 1.20), below
-//   K = 640 to N = 4096 (8192 x 512 at m = 16 1.12). To K = 6144 on the widths above up to m = 12
-//   (0.5 .. 1.09; 20480 x 5120 0.82; not 16384 rows, with which 256 stepped workgroups of 64 rows
-//   fill the chip: 16384 x 2560 1.08); above m = 12 to N = 8192 at K <= 4096 (16383 x 3072 at m = 16
-//   1.10) and to N = 4096 beyond (8192 x 5120 at m = 16 17.8 against 15.6 us). Longer rows to N = 4096
-//   up to m = 12 (0.92 .. 0.99; K > 8064 1.01 .. 1.14: to N = 2048) and to N = 2048 above (4096 x 7680
-//   1.05).
+//   K = 640 to N = 4096 (8192 x 512 at m = 16 1.12). To K = 6144 below N = 16384 up to m = 12 (0.5 ..
+//   1.09; 16384 x 2560, with which 256 stepped workgroups of 64 rows fill the chip, 1.08); above m = 12
+//   to N = 8192 at K <= 4096 (16383 x 3072 at m = 16 1.10) and to N = 4096 beyond (8192 x 5120 at m = 16
+//   17.8 against 15.6 us). Longer rows to N = 4096 up to m = 12 (0.92 .. 0.99; K > 8064 1.01 .. 1.14: to
+//   N = 2048) and to N = 2048 above (4096 x 7680 1.05).
 bool sk8r_shape(int M, int64_t N, int K) {
   if (M < 3 || M > 16 || K < 512 || K > 8192 || sk8_shape(M, K)) return false;
   if (M <= 4) return N >= (M == 3 ? 8192 : 4096) && K >= 1024 && K % 4096 <= 3968;
@@ -3028,8 +3027,7 @@ bool sk8r_shape(int M, int64_t N, int K) {
     return M * N <= 65536 ? N >= (M == 5 ? 4096 : M < 8 && K > 8064 ? 2560 : 2048)
                           : K >= 1024 && ragged_width(N);
   if (K < 1024) return N <= (K < 640 ? 4096 : 8192);
-  if (K <= 6144)
-    return M <= 12 ? N != 16384 && ragged_width(N) : N <= (K <= 4096 ? 8192 : 4096);
+  if (K <= 6144) return M <= 12 ? N < 16384 : N <= (K <= 4096 ? 8192 : 4096);
   return N <= (M <= 12 && K <= 8064 ? 4096 : 2048);
 }
 

@@ -487,5 +487,4 @@ def test_ragged_split_k_rule():
             assert lp(bits, m, 5120, 32768) == "mfma" and lp(bits, m, 5120, 32769) == "splitk"
             assert lp(bits, m, 5120, 49152) == "splitk" and lp(bits, m, 5120, 49153) == "mfma"
     assert lp(4, 4, 2016, 20480) == "mfma" and lp(8, 4, 5120, 128256) == "splitk"
-    assert lp(8, 12, 5120, 20480) == "splitk" and lp(8, 13, 5120, 20480) == "mfma"
     assert lp(8, 9, 2560, 16383) == "splitk" and lp(8, 9, 2560, 16384) == "mfma"
