@@ -3177,8 +3177,8 @@ double stepped_us(int M, int64_t N, int K, int bits, bool symmetric) {
 
 // The K-quartered kernels: 128 x 128 tiles, a round of 256 workgroups and a step of 128 k.
 struct QuarteredUs { double round, step, spread, partial, full; };
-constexpr QuarteredUs kQuarteredUs4 = {10.66, 0.799, 0.088, 0.047, 0.222};
-constexpr QuarteredUs kQuarteredUs8 = {9.8, 1.519, 0.152, 0.053, 0.434};
+constexpr QuarteredUs kQuarteredUs4 = {10.8, 0.797, 0.366, 0.03, 0.2};
+constexpr QuarteredUs kQuarteredUs8 = {8.84, 1.475, 0.152, 0.0, 0.434};
 double quartered_us(int M, int64_t N, int K, int bits) {
   const QuarteredUs& c = bits == 4 ? kQuarteredUs4 : kQuarteredUs8;
   const int64_t gx = (N + 127) / 128, gy = ((int64_t)M + 127) / 128, wgs = gx * gy;

@@ -73,7 +73,7 @@ STEPPED_US = {
     "table4": (5.4, 0.935, 0.234, 0.054, 2.9, 1.1e-6),
     "bits8": (5.6, 0.875, 0.588, 0.136, 5.25, 1.125e-6),
 }
-QUARTERED_US = {4: (10.66, 0.799, 0.088, 0.047, 0.222), 8: (9.8, 1.519, 0.152, 0.053, 0.434)}
+QUARTERED_US = {4: (10.8, 0.797, 0.366, 0.03, 0.2), 8: (8.84, 1.475, 0.152, 0.0, 0.434)}
 
 
 def code_fetches(gx, gy):
