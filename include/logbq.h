@@ -182,25 +182,27 @@ int32_t logbq_encode(const float* w_dev, int64_t n, int64_t k, const logbq_param
  *               so the call is capturable in a HIP graph. Entries are rounded to float16 after
  *               a common power-of-two scaling, exact in the result up to float16 rounding.
  *   y_dev     : device, [m][n] float32, written.
- * Accumulation is float32. Four kernels, chosen from (m, k, n) alone: for 2 <= m <= 32 and
- * k in {1024, 2048, 4096, 8192} (and m <= 16 at k = 14336; there, as above m = 16, only for
- * sign-symmetric codebooks), a split-K
- * dequantize-into-MFMA kernel takes 5 <= m <= 16,
- * m = 4 unless n <= 1024 at k = 8192, m = 3 at n >= 4096, and 17 <= m <= 32 unless m > 20 at
- * k = 8192 and n > 16384 (above m = 16 only for sign-symmetric codebooks; at k = 8192 above
- * m = 16, and for sign-symmetric codebooks on narrow layers -- k = 8192 with n <= 2048 up to
- * m = 8 and n <= 8192 above, k = 4096 with n <= 2048 above m = 12 -- it first zeroes y and two
- * workgroups add their halves of K into each output); otherwise the wavefront-reduced GEMV
- * runs for m <= 8 unless m >= 3 and m * n > 65536; everything else (and shapes whose
- * activations do not fit the GEMV's registers) runs the stepped dequantize-into-MFMA skinny
- * GEMM, except m > 96 at n >= 4096, which runs a K-quartered MFMA GEMM for sign-symmetric
- * codebooks unless ceil(n / 64) * ceil(m / 128) <= 256. The stepped kernel runs in the launch
- * shape a cost model rates cheapest among those whose grid is on the chip at once (at most 256
- * workgroups): 64- or 128-row workgroups, batch blocks of 16 to 128 rows (to 64 for 8-bit codes
- * and codebooks that are not sign-symmetric), and K in one part or (from k = 4096) in two,
- * where y is zeroed first and each part adds into it; with none that fits, 128-row workgroups
- * with the largest batch blocks. logbq_linear_path reports the path, and logbq_linear_kernel
- * the kernel. Results are deterministic for every path.
+ * Accumulation is float32. Five kernels, chosen from (m, k, n) and from whether the codebook is
+ * sign-symmetric (every fitted one is):
+ *   - split-K dequantize-into-MFMA, m <= 32. At k in {1024, 2048, 4096, 8192}: 5 <= m <= 16, m = 4
+ *     unless n <= 1024 at k = 8192, m = 3 at n >= 4096, and 17 <= m <= 32 unless m > 20 at k = 8192
+ *     and n > 16384 (above m = 16 only for sign-symmetric codebooks); at k = 14336 and m <= 16, and
+ *     at any other 512 <= k <= 16384 and 3 <= m <= 16 on the widths where it is the faster, for
+ *     sign-symmetric codebooks. Where two workgroups share the rows (k = 8192 above m = 16,
+ *     k > 8192, narrow layers) it first zeroes y and they add their halves of K into each output.
+ *   - the wavefront-reduced GEMV for the rest of m <= 8 unless m >= 3 and m * n > 65536, and unless
+ *     the activations do not fit its registers;
+ *   - up to m = 128 for the rest: a K-quartered MFMA GEMM for sign-symmetric codebooks at m > 96 and
+ *     n >= 4096 unless ceil(n / 64) <= 256, else the stepped dequantize-into-MFMA skinny GEMM;
+ *   - above m = 128: the prefill MFMA GEMM (k < 2^22, n < 2^21), the K-quartered one (n >= 4096,
+ *     sign-symmetric codebooks) or the stepped one, whichever a model of their times rates cheapest.
+ * The stepped kernel runs in the launch shape a cost model rates cheapest among those whose grid
+ * is on the chip at once (at most 256 workgroups): 64- or 128-row workgroups, batch blocks of 16
+ * to 128 rows (to 64 for 8-bit codes and codebooks that are not sign-symmetric), and K in one part
+ * or (from k = 4096) in two, where y is zeroed first and each part adds into it; with none that
+ * fits, 128-row workgroups with the largest batch blocks. The prefill kernel's batch blocks (64 to
+ * 256 rows) and K parts (one or two) come from its model likewise. logbq_linear_path reports the
+ * path, and logbq_linear_kernel the kernel. Results are deterministic for every path.
  * k == 0 writes zeros. Errors: INVALID_ARG, UNSUPPORTED (k % 32, alignment, or k >= 2^24 on
  * the stepped or K-quartered MFMA kernel), HIP.
  */
@@ -246,10 +248,13 @@ int32_t logbq_dequantize(const uint8_t* codes_dev, int64_t n, int64_t k, const f
  *   y_dev     : device, [m][n] float32, written.
  * Float32 accumulation. For k in {2048, 4096, 8192} a split-K dequantize-into-MFMA kernel
  * takes 5 <= m <= 8 unless n <= 1024 at k >= 4096, m = 3, 4 at n >= 8192, and 9 <= m <= 16
- * unless n > 16384 at k = 8192; otherwise the GEMV runs for m <= 8 unless m >= 5 and
- * m * n > 65536, a K-quartered MFMA GEMM for m > 64 at n >= 16384, and the stepped
+ * unless n > 16384 at k = 8192; at any other 512 <= k <= 8192 it takes 3 <= m <= 16 on the widths
+ * where it is the faster. Otherwise the GEMV runs for m <= 8 unless m >= 5 and
+ * m * n > 65536; up to m = 128 a K-quartered MFMA GEMM for m > 64 at n >= 16384 and the stepped
  * dequantize-into-MFMA skinny GEMM for the rest, in its cost-model launch shape (as for
- * logbq_linear; with K in two parts y is zeroed first). Results are deterministic.
+ * logbq_linear; with K in two parts y is zeroed first); above m = 128 the prefill MFMA GEMM
+ * (k < 2^22, n < 2^21), the K-quartered one (n >= 16384) or the stepped one, as for logbq_linear.
+ * Results are deterministic.
  * Errors: as logbq_linear.
  */
 int32_t logbq_linear8(const uint16_t* x_dev, int64_t m, int64_t k, const uint8_t* codes_dev,
@@ -333,16 +338,19 @@ typedef enum logbq_path {
                               sign-symmetric runs the stepped kernel instead, and where k is
                               not 1, 2, 4, 8 or 14 Ki the GEMV or the stepped kernel          */
   LOGBQ_PATH_MFMA_KQ = 4,  /* K-quartered dequantize-into-MFMA GEMM (4-bit, m > 96, n >= 4096;
-                              8-bit, m > 64, n >= 16384); a 4-bit codebook that is not
-                              sign-symmetric (never a fitted one) runs the stepped kernel     */
-  LOGBQ_PATH_MFMA_PF = 5   /* dequantize-into-MFMA GEMM of prefill, m > 128, k < 2^22         */
+                              8-bit, m > 64, n >= 16384; above m = 128 where it is rated the
+                              cheapest); a 4-bit codebook that is not sign-symmetric (never a
+                              fitted one) runs the stepped or the prefill kernel              */
+  LOGBQ_PATH_MFMA_PF = 5   /* dequantize-into-MFMA GEMM of prefill (m > 128, k < 2^22, n < 2^21,
+                              where it is rated the cheapest)                                 */
 } logbq_path;
 
 /*
  * logbq_linear_path -- the kernel a logbq_linear / logbq_linear8 call of shape (m, k, n)
- * runs (Sec. 3.3 product; the choice is this library's, not the method's). Host only: needs
- * no device and touches none. The choice depends on (bits, m, k, n) alone, so it is the same
- * for every linear of a logbq_linear_multi call.
+ * runs with a fitted (sign-symmetric) codebook (Sec. 3.3 product; the choice is this library's,
+ * not the method's). Host only: needs no device and touches none. The choice depends on (bits, m,
+ * k, n) and the codebook's kind alone, so every linear of a logbq_linear_multi call runs what a
+ * call of its own would run; logbq_linear_kernel tells the kernel for any codebook.
  *   bits     : 4 or 8.
  *   m, k, n  : as logbq_linear; k % 32 == 0.
  *   path_out : host, one int32, written with a logbq_path on success.
@@ -354,8 +362,7 @@ int32_t logbq_linear_path(int32_t bits, int64_t m, int64_t k, int64_t n, int32_t
  * logbq_linear_kernel -- name of the kernel instance (with its template arguments, as a
  * profiler lists it) that reads the codes in a logbq_linear / logbq_linear8 call of shape
  * (m, k, n), e.g. "k_gemv<4, 1, 4, false, 2>" (Sec. 3.3 product; the choice is this
- * library's); a split-K call over workgroup pairs launches k_fill_zero before it, and one
- * that runs its batch in 16-row launches (k = 14336 above m = 16) is named by its first.
+ * library's); a call whose K comes in two parts launches k_fill_zero before it.
  * Host only: needs no device and touches none.
  *   bits, m, k, n : as logbq_linear_path; n fits in int32.
  *   codebook      : host, 2^bits floats, or NULL for a fitted (sign-symmetric) codebook; the

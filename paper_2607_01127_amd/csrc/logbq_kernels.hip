@@ -27,8 +27,8 @@
 //              workgroup, dequantization and staging issued between the MFMAs of the slice before.
 //   k_encode8, k_dequant8, k_gemv<8, ...>, k_mfma2<8, ...>  the same on 8-bit codes.
 //   k_encode_uniform  codes of the asymmetric linear baseline (Sec. 2), for comparisons.
-//   k_gptq_panel, k_gptq_trail  GPTQ calibration with a fixed codebook (one wavefront per row
-//              within a block of 128 columns; the block's errors applied to the later columns).
+//   k_gptq_panel, k_gptq_trail  GPTQ calibration with a fixed codebook (16 lanes per row within a
+//              block of 128 columns; the block's errors applied to the later columns).
 //   k_fit_hist  the device fit's radix-selection passes (Eq. 5 with exact sums): per-bin counts
 //              and exact integer energy sums of |w| binned by its float32 bit pattern.
 //
@@ -768,8 +768,9 @@ __global__ __launch_bounds__(512) void k_gemv(const uint16_t* __restrict__ x,
 // outputs per thread, 32 columns of errors and U rows at a time through LDS. Two rounded
 // operations per product make the VALU its bound: at 8192 x 2048 it runs 43 T of them a second, 54 us
 // on average per block, where 16 x 64 tiles, reading five LDS words per four products, took
-// 117 us. The whole calibration, MI355X: 8192 x 2048 3.87 -> 1.21 ms, 2048 x 2048 1.50 -> 0.61 ms
-// (baseline quantizer 1.62 -> 0.68 ms), 511 x 1824 1.15 -> 0.51 ms.
+// 117 us. The whole calibration, MI355X, a call by itself: 8192 x 2048 3.87 -> 1.19 ms, 2048 x 2048
+// 1.50 -> 0.62 ms (baseline quantizer 1.62 -> 0.69 ms), 511 x 1824 1.15 -> 0.47 ms; calls back to back,
+// a copy of the weights included, 8192 x 2048 3.92 -> 1.14 ms.
 constexpr int kGptqBlock = 128;
 constexpr int kGptqRows = 16;    // rows per panel workgroup (4 wavefronts of 4 rows)
 
@@ -1730,11 +1731,10 @@ __global__ __launch_bounds__(512) void k_mfma_kq8(const uint8_t* __restrict__ co
 // 0 and 1 of step s) and its first reads (slice 3 of step s), and between the last reads of tile
 // s - 2 (slice 2 of step s - 2), whose slot it takes, and its writes.
 //
-// Results do not depend on the launch shape: every output is one sum over K in ascending
-// slices.
-//
-// K may come in two parts (workgroups of gridDim.y = 2, y zeroed beforehand, one atomic add each):
-// every output receives exactly two adds onto zero, which round the same in either order.
+// Every output of a K part is one sum over its slices in ascending order, so results do not depend on
+// BT, but on the number of parts. K may come in two (workgroups of gridDim.y = 2, y zeroed
+// beforehand, one atomic add each): every output receives exactly two adds onto zero, which round
+// the same in either order, so calls of one shape repeat their bits.
 //
 // Codes are looked up in an LDS table of float16 images (8 bits) or pairs of them (4 bits), 256
 // words with one copy per lane (64 KiB) or, where the tiles leave less room, one per lane of a
@@ -2569,9 +2569,9 @@ __global__ __launch_bounds__(fit_threads(PASS)) void k_fit_hist(const float* __r
   const int64_t end = n - begin < C ? n : begin + C;
   const int64_t vend = begin + ((end - begin) & ~int64_t(3));
   // Passes 1 and 2 take U = 4 vectors per thread per iteration, all requested before any is
-  // binned (pass 1 waits on its LDS atomics, and with two workgroups per CU one vector in
-  // flight per thread left HBM idle: 263 -> 244 us and 196 -> 182 us per pass on the
-  // 8192 x 28672 tensor, MI355X); pass 3 bins almost nothing and streams best with U = 1.
+  // binned: pass 1 waits on its LDS atomics, and one vector in flight per thread left HBM idle
+  // (263 -> 244 us and 196 -> 182 us per pass on the 8192 x 28672 tensor, MI355X, measured with
+  // workgroups of 512 threads, two per CU); pass 3 bins almost nothing and streams best with U = 1.
   constexpr int U = PASS == 3 ? 1 : 4;
   for (int64_t i0 = begin + 4 * t; i0 < vend; i0 += 4 * kThreads * U) {
     u32x4 v[U];
@@ -3063,7 +3063,7 @@ int32_t launch_sk8(const uint16_t* x, int M, int K, const LinearJob& j, hipStrea
   return launch_status();
 }
 
-// K-quartered MFMA path on 8-bit codes: m > 64 at N >= 16384 (above m = 128 where wide_path says).
+// K-quartered MFMA path on 8-bit codes: m > 64 at N >= 16384 (above m = 128 where wide_path says so).
 // (K < 2^24 keeps the 128-row buffer descriptor below 2^31 bytes.)
 bool kq8_shape(int M, int64_t N, int K) { return M > 64 && N >= 16384 && K < (1 << 24); }
 
@@ -3139,12 +3139,12 @@ bool pf_fits(int M, int64_t N, int K) {
 // fitted to MI355X measurements (graph replay, codes streamed from HBM). Measured over 4071 shapes
 // and codebooks (m = 129 .. 2048, n = 1024 .. 28672, k = 512 .. 14336, odd ones among them), the
 // kernel taken is within 3 % of the fastest on 95 % of them. Both sides of the lines, us:
-//   stepped / prefill: 1024 x 4096 at m = 300 16.3 / 26.0; 2048 x 8192 at m = 512 37 / 48, at
-//     m = 640 54 / 51; on another 4-bit codebook 11008 x 11008 at m = 192 144 / 82
-//   K-quartered / prefill: 8192 x 8192 at m = 512 78.5 / 95.7; 14336 x 4096 at m = 192 44.8 / 49.5;
-//     28672 x 8192 at m = 192 167 / 124; 8-bit 16384 x 4096 at m = 256 71.0 / 76.3, 28672 x 8192
-//     at m = 129 256 / 136
-//   stepped / K-quartered: 6144 x 4096 at m = 257 29.1 / 37.2; 5120 x 4096 at m = 768 46.4 / 42.0
+//   stepped / prefill: 1024 x 4096 at m = 300 16.3 / 26.0; 2048 x 8192 at m = 512 38 / 49, at
+//     m = 640 55 / 51; on another 4-bit codebook 11008 x 11008 at m = 192 144 / 82
+//   K-quartered / prefill: 8192 x 8192 at m = 512 79 / 96; 14336 x 4096 at m = 192 39 / 46;
+//     28672 x 8192 at m = 192 153 / 116; 8-bit 16384 x 4096 at m = 256 71 / 76, 28672 x 8192 at
+//     m = 129 258 / 142
+//   stepped / K-quartered: 6144 x 4096 at m = 257 29.1 / 37.5; 5120 x 4096 at m = 768 46.4 / 42.0
 //
 // XCDs that fetch the codes of one row block: with gx row blocks the workgroups gx apart, one per
 // batch block, go round-robin to the 8 XCDs, on which 8 / gcd(gx, 8) of them differ.
@@ -3415,9 +3415,9 @@ int32_t launch_sk(const uint16_t* x, int M, int K, const LinearJob* jobs, const 
 // m * N > 65536 (N = 28672 from m = 3, N = 14336 from m = 5; at N = 8192, m = 8 the GEMV is
 // still 1 us faster); the GEMV takes everything else up to m = 8. At 8 bits the stepped MFMA
 // kernel looks up every weight in its LDS table and the GEMV stays ahead to m = 4 on every
-// layer (8192 -> 28672 at m = 3 / 4: 48.0 / 56.1 us vs 57.2 / 57.3 us; at m = 6: 103 vs 57 us). The choice depends only on
-// (m, k, N), so every linear of a grouped call runs the kernel that a single call would run,
-// with the same result bits.
+// layer (8192 -> 28672 at m = 3 / 4: 48.0 / 56.1 us vs 57.2 / 57.3 us; at m = 6: 103 vs 57 us). The
+// choice depends only on (m, k, N) and on whether a 4-bit codebook is sign-symmetric, so every
+// linear of a grouped call runs the kernel that a single call would run, with the same result bits.
 //
 // Above m = 128 the cheapest by wide_path's models.
 //
