@@ -255,7 +255,8 @@ def test_linear_path_rule():
     assert lp(4, 17, 14336, 4096) == "mfma" and lp(4, 48, 14336, 4096) == "mfma"
     assert lp(4, 96, 8192, 28672) == "mfma"
     # K-quartered MFMA GEMM: 4-bit, m > 96 at N >= 4096, unless the stepped kernel's 64-row
-    # grid fits on the chip (ceil(N / 64) x ceil(m / 128) <= 256 workgroups)
+    # grid fits on the chip (ceil(N / 64) <= 256 workgroups); above m = 128 where it is rated the
+    # cheapest (test_wide_path_rule)
     assert lp(4, 128, 8192, 28672) == "mfma_kq" and lp(4, 97, 1024, 16448) == "mfma_kq"
     assert lp(4, 97, 1024, 4096) == "mfma" and lp(4, 128, 1024, 16384) == "mfma"
     assert lp(4, 129, 1024, 8192) == "mfma" and lp(4, 129, 4096, 12288) == "mfma_kq"
